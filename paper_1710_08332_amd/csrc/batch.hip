@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(kBatchThreads)
       // complete in memory; fold them in chunk order (the fold's own
       // barriers also free its LDS before the next tile)
       const BInst I = insts[fold];
-      final_fold<PlainF32, kFinalPlain, true, 8, 4>(partials + I.part_off, I.G, I.out, 0, lds);
+      final_fold<PlainF32, kFinalPlain, true>(partials + I.part_off, I.G, I.out, 0, lds);
       if (threadIdx.x == 0)
         __hip_atomic_store(arrive + fold, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -336,7 +336,7 @@ extern "C" dpia_status dpia_batch_plan_create(const dpia_instance* inst, int32_t
   P->nred = static_cast<int32_t>(red.size());
   P->npartials = npart;
   P->lds_bytes = lds;
-  P->lds_one_bytes = std::max(lds, kFoldBlock * sizeof(float));
+  P->lds_one_bytes = std::max(lds, kFoldLds);
   P->inst_off = 0;
   P->tile_off = align_up(sizeof(BInst) * bi.size());
   P->red_off = P->tile_off + align_up(sizeof(BTile) * tiles.size());
@@ -413,7 +413,7 @@ dpia_status batch_launch(const dpia_batch_plan* plan, void* ws, size_t ws_bytes,
     if (e == hipSuccess && plan->nred > 0) {
       void* a2[] = {&insts, &red, &partials};
       e = hipLaunchKernel(reinterpret_cast<const void*>(batch_fold_kernel), dim3(plan->nred),
-                          dim3(64), a2, kFoldBlock * sizeof(float), hs);
+                          dim3(64), a2, kFoldLds, hs);
     }
   }
   if (e != hipSuccess) return hip_fail(e, "dpia_batch_run launch");

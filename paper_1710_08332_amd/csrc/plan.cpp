@@ -270,8 +270,7 @@ dpia_status make_plan(const dpia_strategy* s, dpia_op op, dpia_dtype dt, int64_t
   }
   if ((op == DPIA_OP_DOT || op == DPIA_OP_ASUM) && q.passes == 1) {
     // the last work-group of a 1-pass launch runs the final fold
-    size_t fold = static_cast<size_t>(kFoldBlock) * q.acc_bytes;
-    if (fold > lds) lds = fold;
+    if (kFoldLds > lds) lds = kFoldLds;
   }
   lds = round_up(lds + 16, 16);
 #ifndef DPIA_LDS_CAP

@@ -12,8 +12,8 @@ namespace dpia {
 
 // Bytes of one 16-byte vector load, the widest global load used.
 constexpr int kVecBytes = 16;
-// Chunk results staged through LDS per block by the final sequential fold.
-constexpr int kFoldBlock = 2048;
+// LDS bytes of the fold over the chunk values (fold.h).
+constexpr size_t kFoldLds = 320;
 // Alignment of the sections of a workspace.
 constexpr size_t kWsAlign = 256;
 // LDS staging of the contiguous order: elements per lane per tile, and the

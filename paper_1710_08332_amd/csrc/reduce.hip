@@ -87,8 +87,7 @@ __global__ void __launch_bounds__(MAXT) reduce_kernel(Op op, ReduceArgs a) {
     }
     __syncthreads();
     if (is_last) {
-      final_fold<typename Op::Arith, FINAL, true, (sizeof(T) > 4 ? 4 : 8), 4>(
-          partials, a.values, a.out, a.out_f64, lds);
+      final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds);
       if (threadIdx.x == 0)   // leave the counter at zero for the next call
         __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -194,8 +193,7 @@ __global__ void __launch_bounds__(kWave*(1 + kFedLoaders)) fed_reduce_kernel(Op 
     }
     __syncthreads();
     if (is_last) {
-      final_fold<typename Op::Arith, FINAL, true, (sizeof(T) > 4 ? 4 : 8), 4>(
-          partials, a.values, a.out, a.out_f64, lds);
+      final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds);
       if (threadIdx.x == 0)
         __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -203,10 +201,10 @@ __global__ void __launch_bounds__(kWave*(1 + kFedLoaders)) fed_reduce_kernel(Op 
 }
 
 template <class A, int FINAL>
-__global__ void __launch_bounds__(256) final_kernel(const typename A::T* partials, int64_t G,
-                                                    void* out, int out_f64) {
+__global__ void __launch_bounds__(1024) final_kernel(const typename A::T* partials, int64_t G,
+                                                     void* out, int out_f64) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  final_fold<A, FINAL>(partials, G, out, out_f64, reinterpret_cast<typename A::T*>(lds_raw));
+  final_fold<A, FINAL>(partials, G, out, out_f64, lds_raw);
 }
 
 template <class Op>
@@ -324,8 +322,6 @@ hipError_t launch_fed(const Plan& p, const Op& op, const ReduceArgs& a, int rows
   // the ring from the start of the LDS: the kernel's combines within one
   // wavefront need no LDS, and the 1-pass fold uses it after the chunks
   size_t lds = static_cast<size_t>(fed_ring_floats()) * sizeof(float);
-  const size_t fold = static_cast<size_t>(kFoldBlock) * sizeof(typename Op::T);
-  if (fold > lds) lds = fold;
   lds = (lds + 16 + 15) / 16 * 16;
   Op op_copy = op;
   ReduceArgs a_copy = a;
@@ -389,7 +385,9 @@ hipError_t launch_chunks(const Plan& p, const Op& op, const ReduceArgs& a, hipSt
   });
 }
 
-// The outer reduceSeq over G chunk values, as a kernel of its own.
+// The outer reduceSeq over G chunk values, as a kernel of its own: 4
+// wavefronts while one block of theirs holds the values, else 16.
+constexpr int64_t kFoldWide = 4096;
 template <class Op, int FINAL>
 hipError_t launch_fold(int64_t G, const void* partials, void* out, int out_f64,
                        hipStream_t stream) {
@@ -397,8 +395,9 @@ hipError_t launch_fold(int64_t G, const void* partials, void* out, int out_f64,
   const T* pp = static_cast<const T*>(partials);
   void* args[] = {&pp, &G, &out, &out_f64};
   auto kern = final_kernel<typename Op::Arith, FINAL>;
-  return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(1), dim3(256), args,
-                         kFoldBlock * sizeof(T), stream);
+  const int threads = G > kFoldWide ? 1024 : 256;
+  return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(1), dim3(threads), args,
+                         kFoldLds, stream);
 }
 
 // Both passes of a reduction: chunk values into `partials`, then the outer
