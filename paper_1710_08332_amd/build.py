@@ -24,7 +24,12 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libdpia.so")
 
-HIP_SOURCES = ["reduce.hip", "gemv.hip", "batch.hip", "map.hip", "module.hip", "stream.hip"]
+# (the slowest to build first)
+HIP_SOURCES = ["reduce_dot.hip", "reduce_dot_deep.hip", "reduce_dot_deeper.hip", "reduce_asum.hip",
+               "reduce_kahan.hip", "reduce_sum2.hip", "reduce_i32.hip", "gemv_f32.hip",
+               "gemv_f32_cached.hip", "gemv_fp8.hip", "gemv_fp8_long.hip", "gemv_bf16.hip",
+               "gemv_fed.hip", "gemv_i32.hip", "batch.hip", "map.hip", "reduce.hip", "gemv.hip",
+               "module.hip", "stream.hip"]
 CPP_SOURCES = ["plan.cpp"]
 
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")

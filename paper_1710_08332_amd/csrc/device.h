@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "plan.h"
 
@@ -374,6 +375,33 @@ __device__ __forceinline__ void lane_folds(const View& view, bool active, int t,
     have = have < 0 ? 0 : (have > C ? C : have);
     nfull = have / NV;
   }
+  // a batch of N steps from step i, in the remainder.  (Its offsets are kept
+  // apart from the main loop's, which the compiler would otherwise hold more
+  // addresses for: 137 registers, not 105, in the headline gemv.)
+  int from = start;
+  auto batch = [&](auto nc, int i) {
+    constexpr int N = decltype(nc)::value;
+    const int o = from + i * step;
+    if constexpr (HasRaw<View>::value) {
+      typename View::template Raw<NV> r[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) view.template load_raw<NV>(o + u * step, r[u]);
+      __builtin_amdgcn_sched_barrier(0);   // issue the whole batch first
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        Term z[NV];
+        View::template expand<NV>(r[u], z);
+        fold_vec(z, NV);
+      }
+    } else {
+      Term z[N][NV];
+#pragma unroll
+      for (int u = 0; u < N; ++u) view.template load<NV>(o + u * step, z[u]);
+      __builtin_amdgcn_sched_barrier(0);   // issue the whole batch first
+#pragma unroll
+      for (int u = 0; u < N; ++u) fold_vec(z[u], NV);
+    }
+  };
   const int nb = nfull / U;
   for (int j = 0; j < nb; ++j) {
     const int o = start + j * U * step;
@@ -382,7 +410,9 @@ __device__ __forceinline__ void lane_folds(const View& view, bool active, int t,
       // just before its fold
       typename View::template Raw<NV> r[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) view.template load_raw<NV>(o + u * step, r[u]);
+      for (int u = 0; u < U; ++u) view.template load_raw_x<NV>(o + u * step, r[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) view.template load_raw_a<NV>(o + u * step, r[u]);
       __builtin_amdgcn_sched_barrier(0);   // issue the whole batch first
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -399,33 +429,44 @@ __device__ __forceinline__ void lane_folds(const View& view, bool active, int t,
       for (int u = 0; u < U; ++u) fold_vec(z[u], NV);
     }
   }
-  for (int i = nb * U; i < nfull; ++i) {
-    Term z[NV];
-    view.template load<NV>(start + i * step, z);
-    fold_vec(z, NV);
+  // what is left, in batches of U/2, U/4, ..., 1 steps: log2 U waits on
+  // memory, not U - 1 (rows of 2,080 over 256 lanes: the benchmark's 4,608
+  // batched instances 2,315 -> 2,051 us)
+  if (__builtin_expect(nfull % U != 0, 0)) {
+    int i = nb * U;
+    asm("" : "+v"(from));
+    if constexpr (U > 8)
+      if (nfull & 8) batch(std::integral_constant<int, 8>{}, i), i += 8;
+    if constexpr (U > 4)
+      if (nfull & 4) batch(std::integral_constant<int, 4>{}, i), i += 4;
+    if constexpr (U > 2)
+      if (nfull & 2) batch(std::integral_constant<int, 2>{}, i), i += 2;
+    if constexpr (U > 1)
+      if (nfull & 1) batch(std::integral_constant<int, 1>{}, i);
   }
   // the last, partly existing row (strided) or the last elements of a lane
-  // (contiguous), one element at a time
+  // (contiguous): its elements are loaded together, then folded
+  const int o = start + nfull * step;
+  int part;
   if constexpr (ORDER == kStrided) {
-    if (nfull < C) {
-      const int o = start + nfull * step;
+    part = nfull < C ? limit - o : 0;
+    part = part < 0 ? 0 : (part > NV ? NV : part);
+  } else {
+    part = limit - t * C;
+    part = (part < 0 ? 0 : (part > C ? C : part)) - nfull * NV;
+  }
+  if (__builtin_expect(part > 0, 0)) {
+    Term z[NV];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        if (o + v < limit) {
-          Term z[1];
-          view.template load<1>(o + v, z);
-          acc[v] = Op::step(z[0], acc[v]);
-        }
+    for (int v = 0; v < NV; ++v) {
+      if (v < part) {
+        Term one[1];
+        view.template load<1>(o + v, one);
+        z[v] = one[0];
       }
     }
-  } else {
-    int have = limit - t * C;
-    have = have < 0 ? 0 : (have > C ? C : have);
-    for (int k = nfull * NV; k < have; ++k) {
-      Term z[1];
-      view.template load<1>(start + k, z);
-      acc[0] = Op::step(z[0], acc[0]);
-    }
+    __builtin_amdgcn_sched_barrier(0);
+    fold_vec(z, part);
   }
 }
 
@@ -666,45 +707,30 @@ __device__ __forceinline__ void contiguous_staged_codes(const View& view, bool a
   }
 }
 
-template <class V, class = void>
-struct StageableCodes {
-  static constexpr bool value = false;
-};
-template <class V>
-struct StageableCodes<V, decltype(void(V::kStageableCodes))> {
-  static constexpr bool value = V::kStageableCodes;
-};
-
-// `stage`: this wavefront's LDS staging region (contiguous order, stageable
-// views; with SS, also the strided order with one thread per chunk) or
-// nullptr for direct loads.  The choice is uniform per launch.
-template <class Op, int ORDER, int NV, int COMBINE, bool SS = false, class View>
+// STAGED: the lanes are folded through `stage`, this wavefront's LDS staging
+// region (the contiguous order, stageable views; the strided order with one
+// thread per chunk), else from direct loads.  A build of its own each: with
+// both in one kernel the direct path of contiguous gemv rows had the staged
+// path's 199 registers, 2 wavefronts per SIMD.
+template <class Op, int ORDER, int NV, int COMBINE, bool STAGED = false, class View>
 __device__ __forceinline__ typename Op::T chunk_value(const View& view, bool active, int t,
                                                       int team, int L, int C, int limit,
                                                       typename Op::T* scratch,
                                                       float* stage = nullptr) {
   constexpr int NL = (ORDER == kStrided) ? NV : 1;
   typename Op::T acc[NL];
-  if constexpr (ORDER == kContiguous && View::kStageable) {
-    if (stage != nullptr) {
-      contiguous_staged<Op, 1>(view, active, t, C, limit, acc, stage);
-      return combine_lanes<typename Op::Arith, NL, COMBINE>(acc, t, team, L, scratch);
-    }
-  } else if constexpr (ORDER == kStrided && SS && View::kStageable && 4 % NV == 0) {
+  if constexpr (STAGED && ORDER == kContiguous && View::kStageable) {
+    contiguous_staged<Op, 1>(view, active, t, C, limit, acc, stage);
+  } else if constexpr (STAGED && ORDER == kContiguous) {
+    contiguous_staged_codes<Op>(view, active, t, C, limit, acc[0], stage);
+  } else if constexpr (STAGED) {
     // one thread holds all NV = L lanes of its chunk (team 1; the plan
     // stages only then): its chunk is C * NV contiguous elements, element e
     // belonging to lane e % NV, which contiguous_staged folds as components
-    if (stage != nullptr) {
-      contiguous_staged<Op, NV>(view, active, 0, C, limit, acc, stage);
-      return combine_lanes<typename Op::Arith, NL, COMBINE>(acc, t, team, L, scratch);
-    }
-  } else if constexpr (ORDER == kContiguous && StageableCodes<View>::value) {
-    if (stage != nullptr) {
-      contiguous_staged_codes<Op>(view, active, t, C, limit, acc[0], stage);
-      return combine_lanes<typename Op::Arith, NL, COMBINE>(acc, t, team, L, scratch);
-    }
+    contiguous_staged<Op, NV>(view, active, 0, C, limit, acc, stage);
+  } else {
+    lane_folds<Op, ORDER, NV>(view, active, t, L, C, limit, acc);
   }
-  lane_folds<Op, ORDER, NV>(view, active, t, L, C, limit, acc);
   return combine_lanes<typename Op::Arith, NL, COMBINE>(acc, t, team, L, scratch);
 }
 
@@ -729,23 +755,20 @@ struct ShiftedView {
 // out[g * cv ...], cv = VEC, or L * VEC uncombined, in lane then component
 // order (asScalar VEC of the join), with device-coherent stores.  All threads of the work-group call this
 // together (the combine has barriers).
-// `stage`: as for chunk_value (the contiguous order, staged per wavefront).
-template <class Op, int ORDER, int NV, int COMBINE, int VEC, class View>
+// STAGED, `stage`: as for chunk_value (the contiguous order).
+template <class Op, int ORDER, int NV, int COMBINE, int VEC, bool STAGED, class View>
 __device__ __forceinline__ void chunk_values_wide(const View& view, bool active, int t, int team,
                                                   int L, int C, int limit,
                                                   typename Op::T* scratch, typename Op::T* out,
                                                   int64_t g, float* stage = nullptr) {
   using T = typename Op::T;
-  constexpr bool kStaged = ORDER == kContiguous && View::kStageable;
+  static_assert(!STAGED || ORDER == kContiguous, "vector lanes are staged in the contiguous order");
   if constexpr (VEC == 1) {
     static_assert(COMBINE == kNone, "scalar combined chunks use chunk_value");
     constexpr int NL = (ORDER == kStrided) ? NV : 1;
     T acc[NL];
-    if constexpr (kStaged) {
-      if (stage != nullptr)
-        contiguous_staged<Op, 1>(view, active, t, C, limit, acc, stage);
-      else
-        lane_folds<Op, ORDER, NV>(view, active, t, L, C, limit, acc);
+    if constexpr (STAGED) {
+      contiguous_staged<Op, 1>(view, active, t, C, limit, acc, stage);
     } else {
       lane_folds<Op, ORDER, NV>(view, active, t, L, C, limit, acc);
     }
@@ -765,14 +788,9 @@ __device__ __forceinline__ void chunk_values_wide(const View& view, bool active,
       // vector lane t takes vectors t*C .. t*C + C-1: within the lane's row of
       // VEC*C elements, component j takes elements j, j + VEC, ..., the
       // strided order over VEC lanes
-      bool staged = false;
-      if constexpr (kStaged) {
-        if (stage != nullptr) {
-          contiguous_staged<Op, VEC>(view, active, t, C, limit, acc, stage);
-          staged = true;
-        }
-      }
-      if (!staged) {
+      if constexpr (STAGED) {
+        contiguous_staged<Op, VEC>(view, active, t, C, limit, acc, stage);
+      } else {
         const int base = t * VEC * C;
         int have = limit - base;
         have = have < 0 ? 0 : (have > VEC * C ? VEC * C : have);

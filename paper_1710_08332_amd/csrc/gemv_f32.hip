@@ -1,0 +1,10 @@
+// Kernels and launches of one matrix type (built apart from the others, so
+// that they build in parallel).
+#include "gemv.h"
+
+namespace dpia {
+
+template hipError_t launch_gemv<GemvF32, 4>(const Plan&, const GemvF32&, int64_t, int64_t,
+                                              hipStream_t, int);
+
+}  // namespace dpia

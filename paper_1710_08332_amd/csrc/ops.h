@@ -206,6 +206,7 @@ struct GemvF32Acc {
   // 43.3 us).  The narrow formats stream A with 16-element batches
   // (row-blocked kernel).  x is reused by every row and stays cached.
   static constexpr bool kF32 = std::is_same<E, float>::value;
+  static constexpr bool kF32Rows = kF32;
   static constexpr int kBatchElems =
       BATCH ? BATCH
             : (kF32 ? DPIA_F32_GEMV_BATCH_ELEMS
@@ -213,8 +214,7 @@ struct GemvF32Acc {
   static constexpr bool kStreamA = STREAM >= 0 ? STREAM != 0 : (!kF32 || DPIA_F32_GEMV_STREAM_A);
   struct View {
     static constexpr bool kStageable = std::is_same<E, float>::value;
-    // 1- and 2-byte codes: staged by contiguous_staged_codes
-    static constexpr bool kStageableCodes = !std::is_same<E, float>::value;
+    // (1- and 2-byte codes are staged by contiguous_staged_codes)
     using Code = E;
     static constexpr int kOps = 2;
     const E* a;
@@ -233,9 +233,17 @@ struct GemvF32Acc {
       float x[NV];
     };
     template <int NV>
-    __device__ __forceinline__ void load_raw(int off, Raw<NV>& r) const {
+    __device__ __forceinline__ void load_raw_a(int off, Raw<NV>& r) const {
       vload<E, NV, kStreamA>(a + off, r.a);
+    }
+    template <int NV>
+    __device__ __forceinline__ void load_raw_x(int off, Raw<NV>& r) const {
       vload<float, NV, false>(x + off, r.x);   // x is reused by every row: cached
+    }
+    template <int NV>
+    __device__ __forceinline__ void load_raw(int off, Raw<NV>& r) const {
+      load_raw_a<NV>(off, r);
+      load_raw_x<NV>(off, r);
     }
     template <int NV>
     __device__ __forceinline__ static void expand(const Raw<NV>& r, Term (&z)[NV]) {
@@ -339,6 +347,7 @@ using GemvFP8Long = GemvF32Acc<uint8_t, DecodeFP8, 64>;
 
 struct GemvU32 {
   static constexpr bool kRowBlockable = false;
+  static constexpr bool kF32Rows = false;
   using Arith = PlainU32;
   using T = uint32_t;
   using Term = GTermU;
