@@ -37,20 +37,37 @@ class Strategy:
                               self.wg_combine, self.passes, self.accum, self.final_f64,
                               self.rows_per_wg, self.row_parts, self.max_grid, self.vec_width)
 
+    def _ref(self):
+        """A pointer to this strategy's descriptor, which is made once: the
+        fields cannot change, and the library only reads it."""
+        r = self.__dict__.get("_c")
+        if r is None:
+            r = self.__dict__["_c"] = ctypes.pointer(self.c())
+        return r
+
+    def __getstate__(self):
+        # (copies and pickles hold the fields alone)
+        return {k: v for k, v in self.__dict__.items() if k != "_c"}
+
     def with_(self, **kw) -> "Strategy":
         return replace(self, **kw)
 
 
 def strategy_check(s: Strategy, op: int, dtype: int, m: int, n: int) -> int:
     """Validates ``s`` for the problem; returns the workspace size in bytes."""
-    cs = s.c()
     ws = ctypes.c_size_t(0)
-    _lib.check(_lib.lib().dpia_strategy_check(ctypes.byref(cs), op, dtype, m, n,
+    _lib.check(_lib.lib().dpia_strategy_check(s._ref(), op, dtype, m, n,
                                               ctypes.byref(ws)), "dpia_strategy_check")
     return ws.value
 
 
 # ------------------------------------------------------------ torch glue
+
+# A call of a few thousand elements takes the GPU about 4 us, so the binding
+# keeps to what a call needs: addresses go to ctypes as plain integers, the
+# descriptor is made once per strategy, and the current stream's handle is
+# read without making a stream object (a dot of 4,099 elements: 9.1 us a call
+# before, see the file of timed cases).
 
 def _torch():
     import torch
@@ -61,14 +78,17 @@ _DT = {}
 
 
 def _dtype_code(t) -> int:
-    torch = _torch()
-    if not _DT:
-        _DT.update({torch.float32: F32, torch.float64: F64, torch.int32: I32,
-                    torch.uint32: I32, torch.bfloat16: BF16, torch.uint16: BF16,
-                    torch.float8_e4m3fn: FP8_E4M3, torch.uint8: FP8_E4M3})
-    if t.dtype not in _DT:
-        raise TypeError(f"unsupported tensor dtype {t.dtype}")
-    return _DT[t.dtype]
+    code = _DT.get(t.dtype)
+    if code is None:
+        torch = _torch()
+        if not _DT:
+            _DT.update({torch.float32: F32, torch.float64: F64, torch.int32: I32,
+                        torch.uint32: I32, torch.bfloat16: BF16, torch.uint16: BF16,
+                        torch.float8_e4m3fn: FP8_E4M3, torch.uint8: FP8_E4M3})
+        if t.dtype not in _DT:
+            raise TypeError(f"unsupported tensor dtype {t.dtype}")
+        code = _DT[t.dtype]
+    return code
 
 
 def _dev(t):
@@ -76,13 +96,29 @@ def _dev(t):
         raise ValueError("tensors must be on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensors must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_current = None
+
+
+def _current_stream():
+    """The handle of torch's current stream on its current device."""
+    global _current
+    if _current is None:
+        torch = _torch()
+        C = torch._C
+        if hasattr(C, "_cuda_getCurrentRawStream") and hasattr(C, "_cuda_getDevice"):
+            torch.cuda.current_stream()         # torch's GPU state is set up
+            raw, device = C._cuda_getCurrentRawStream, C._cuda_getDevice
+            _current = lambda: raw(device())    # noqa: E731
+        else:
+            _current = lambda: torch.cuda.current_stream().cuda_stream   # noqa: E731
+    return _current()
 
 
 def _stream(stream):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return stream.cuda_stream if stream is not None else _current_stream()
 
 
 def workspace(s: Strategy, op: int, dtype: int, m: int, n: int, device="cuda"):
@@ -95,24 +131,23 @@ def workspace(s: Strategy, op: int, dtype: int, m: int, n: int, device="cuda"):
 
 def _ws(ws):
     if ws is None:
-        return ctypes.c_void_p(0), 0
-    return _dev(ws), ws.numel() * ws.element_size()
+        return None, 0
+    return _dev(ws), ws.nbytes
 
 
 def dot(x, y, s: Strategy, out=None, ws=None, out_dtype=None, stream=None):
-    torch = _torch()
     dt = _dtype_code(x)
     if _dtype_code(y) != dt:
         raise TypeError("x and y must have the same dtype")
     n = x.numel()
     if out is None:
+        torch = _torch()
         od = out_dtype or (torch.float64 if (s.accum != PLAIN and s.final_f64) else x.dtype)
         out = torch.empty(1, dtype=od, device=x.device)
     if ws is None:
         ws = workspace(s, OP_DOT, dt, 0, n, x.device)
-    cs = s.c()
     w, wb = _ws(ws)
-    _lib.check(_lib.lib().dpia_dot(ctypes.byref(cs), dt, n, _dev(x), _dev(y), _dev(out),
+    _lib.check(_lib.lib().dpia_dot(s._ref(), dt, n, _dev(x), _dev(y), _dev(out),
                                    _dtype_code(out), w, wb, _stream(stream)), "dpia_dot")
     return out
 
@@ -123,23 +158,21 @@ def dot_noalloc(x, y, s: Strategy, out, stream=None):
     dt = _dtype_code(x)
     if _dtype_code(y) != dt:
         raise TypeError("x and y must have the same dtype")
-    cs = s.c()
-    _lib.check(_lib.lib().dpia_dot_noalloc(ctypes.byref(cs), dt, x.numel(), _dev(x), _dev(y),
+    _lib.check(_lib.lib().dpia_dot_noalloc(s._ref(), dt, x.numel(), _dev(x), _dev(y),
                                            _dev(out), _dtype_code(out), _stream(stream)),
                "dpia_dot_noalloc")
     return out
 
 
 def asum(x, s: Strategy, out=None, ws=None, stream=None):
-    torch = _torch()
     n = x.numel()
     if out is None:
+        torch = _torch()
         out = torch.empty(1, dtype=torch.float32, device=x.device)
     if ws is None:
         ws = workspace(s, OP_ASUM, F32, 0, n, x.device)
-    cs = s.c()
     w, wb = _ws(ws)
-    _lib.check(_lib.lib().dpia_asum(ctypes.byref(cs), _dtype_code(x), n, _dev(x), _dev(out),
+    _lib.check(_lib.lib().dpia_asum(s._ref(), _dtype_code(x), n, _dev(x), _dev(out),
                                     _dtype_code(out), w, wb, _stream(stream)), "dpia_asum")
     return out
 
@@ -148,19 +181,18 @@ def gemv(A, x, s: Strategy, y=None, row_scale=None, a_dtype=None, stream=None):
     """y = A x.  ``A`` is a 2-D row-major tensor (float32, bfloat16 / uint16
     codes, float8_e4m3fn / uint8 codes, or int32); ``a_dtype`` overrides the
     element type read from A's dtype."""
-    torch = _torch()
     m, k = A.shape
     adt = a_dtype if a_dtype is not None else _dtype_code(A)
     lda = A.stride(0)
     if A.stride(1) != 1:
         raise ValueError("A must be row-major")
     if y is None:
+        torch = _torch()
         y = torch.empty(m, dtype=torch.int32 if adt == I32 else torch.float32, device=A.device)
-    cs = s.c()
-    sc = _dev(row_scale) if row_scale is not None else ctypes.c_void_p(0)
-    _lib.check(_lib.lib().dpia_gemv(ctypes.byref(cs), adt, m, k, lda,
-                                    ctypes.c_void_p(A.data_ptr()), sc, _dev(x), _dev(y),
-                                    ctypes.c_void_p(0), 0, _stream(stream)), "dpia_gemv")
+    sc = _dev(row_scale) if row_scale is not None else None
+    _lib.check(_lib.lib().dpia_gemv(s._ref(), adt, m, k, lda,
+                                    A.data_ptr(), sc, _dev(x), _dev(y),
+                                    None, 0, _stream(stream)), "dpia_gemv")
     return y
 
 
@@ -172,10 +204,9 @@ def gemv_blas(alpha: float, A, x, beta: float, y, s: Strategy, row_scale=None, a
     adt = a_dtype if a_dtype is not None else _dtype_code(A)
     if A.stride(1) != 1:
         raise ValueError("A must be row-major")
-    cs = s.c()
-    sc = _dev(row_scale) if row_scale is not None else ctypes.c_void_p(0)
-    _lib.check(_lib.lib().dpia_gemv_blas(ctypes.byref(cs), adt, m, k, A.stride(0), float(alpha),
-                                         ctypes.c_void_p(A.data_ptr()), sc, _dev(x), float(beta),
+    sc = _dev(row_scale) if row_scale is not None else None
+    _lib.check(_lib.lib().dpia_gemv_blas(s._ref(), adt, m, k, A.stride(0), float(alpha),
+                                         A.data_ptr(), sc, _dev(x), float(beta),
                                          _dev(y), _stream(stream)), "dpia_gemv_blas")
     return y
 
@@ -184,8 +215,7 @@ def scal(alpha: float, x, s: Strategy, y=None, stream=None):
     """y = alpha * x (y may be x: in place)."""
     if y is None:
         y = _torch().empty_like(x)
-    cs = s.c()
-    _lib.check(_lib.lib().dpia_scal(ctypes.byref(cs), _dtype_code(x), x.numel(), float(alpha),
+    _lib.check(_lib.lib().dpia_scal(s._ref(), _dtype_code(x), x.numel(), float(alpha),
                                     _dev(x), _dev(y), _stream(stream)), "dpia_scal")
     return y
 
@@ -219,16 +249,15 @@ def chunks(op: int, s: Strategy, x, y=None, out=None, stream=None):
     """The mapWorkgroup level of a dot (op=OP_DOT) or asum (OP_ASUM): the
     chunks' values (``values_per_chunk`` each; 4 bytes, or 8 for a Kahan
     pair)."""
-    torch = _torch()
     n = x.numel()
     dt = _dtype_code(x)
     vb = 8 if s.accum != PLAIN else 4
     if out is None:
+        torch = _torch()
         out = torch.empty(max(1, num_chunks(s, n) * values_per_chunk(s)) * vb, dtype=torch.uint8,
                           device=x.device)
-    cs = s.c()
-    yp = _dev(y) if y is not None else ctypes.c_void_p(0)
-    _lib.check(_lib.lib().dpia_chunks(ctypes.byref(cs), op, dt, n, _dev(x), yp, _dev(out),
+    yp = _dev(y) if y is not None else None
+    _lib.check(_lib.lib().dpia_chunks(s._ref(), op, dt, n, _dev(x), yp, _dev(out),
                                       out.numel() * out.element_size(), _stream(stream)),
                "dpia_chunks")
     return out
@@ -237,13 +266,12 @@ def chunks(op: int, s: Strategy, x, y=None, out=None, stream=None):
 def fold(op: int, s: Strategy, chunk_values, n: int, dtype: int, out=None, out_dtype=None,
          stream=None):
     """The outer reduceSeq of the strategy over chunk values from ``chunks``."""
-    torch = _torch()
     if out is None:
+        torch = _torch()
         od = out_dtype or (torch.float64 if (s.accum != PLAIN and s.final_f64) else
                            (torch.int32 if dtype == I32 else torch.float32))
         out = torch.empty(1, dtype=od, device=chunk_values.device)
-    cs = s.c()
-    _lib.check(_lib.lib().dpia_fold(ctypes.byref(cs), op, dtype, n, _dev(chunk_values),
+    _lib.check(_lib.lib().dpia_fold(s._ref(), op, dtype, n, _dev(chunk_values),
                                     _dev(out), _dtype_code(out), _stream(stream)), "dpia_fold")
     return out
 
@@ -273,12 +301,12 @@ class BatchPlan:
                 if A.stride(1) != 1:
                     raise ValueError("A must be row-major")
                 c.m, c.n, c.lda = A.shape[0], A.shape[1], A.stride(0)
-                c.a, c.b = A.data_ptr(), _dev(d["x"]).value
+                c.a, c.b = A.data_ptr(), _dev(d["x"])
             else:
                 c.m, c.n, c.lda = 0, d["x"].numel(), 0
-                c.a = _dev(d["x"]).value
-                c.b = _dev(d["y"]).value if d["op"] == OP_DOT else None
-            c.out = _dev(d["out"]).value
+                c.a = _dev(d["x"])
+                c.b = _dev(d["y"]) if d["op"] == OP_DOT else None
+            c.out = _dev(d["out"])
         cs = (_lib.CStrategy * max(1, len(strategies)))(*[s.c() for s in strategies])
         h = ctypes.c_void_p(0)
         _lib.check(L.dpia_batch_plan_create(arr, n, cs, len(strategies), ctypes.byref(h)),

@@ -37,6 +37,15 @@ int widest_vector(int cap, std::initializer_list<int64_t> vals) {
   return v;
 }
 
+// An error's text (put together only where there is one: a stream costs more
+// than the rest of a plan).
+template <class... P>
+std::string text(const P&... parts) {
+  std::ostringstream os;
+  (os << ... << parts);
+  return os.str();
+}
+
 dpia_status fail(std::string* detail, dpia_status st, const std::string& msg) {
   if (detail) *detail = msg;
   return st;
@@ -61,11 +70,10 @@ size_t elem_bytes(dpia_dtype dt) {
 
 dpia_status make_plan(const dpia_strategy* s, dpia_op op, dpia_dtype dt, int64_t m,
                       int64_t n, Plan* p, std::string* detail) {
-  std::ostringstream os;
   if (!s) return fail(detail, DPIA_ERR_NULL, "strategy descriptor is NULL");
   if (s->abi_version != DPIA_ABI_VERSION) {
-    os << "descriptor abi_version " << s->abi_version << " != library " << DPIA_ABI_VERSION;
-    return fail(detail, DPIA_ERR_ABI, os.str());
+    return fail(detail, DPIA_ERR_ABI,
+                text("descriptor abi_version ", s->abi_version, " != library ", DPIA_ABI_VERSION));
   }
   if (op != DPIA_OP_DOT && op != DPIA_OP_ASUM && op != DPIA_OP_GEMV && op != DPIA_OP_SCAL)
     return fail(detail, DPIA_ERR_STRATEGY, "unknown operation");
@@ -145,15 +153,15 @@ dpia_status make_plan(const dpia_strategy* s, dpia_op op, dpia_dtype dt, int64_t
     int64_t k = n;
     if (m < 0 || k < 0) return fail(detail, DPIA_ERR_SHAPE, "negative gemv size");
     if (m % q.R) {
-      os << "m = " << m << " is not a multiple of rows_per_wg = " << q.R;
-      return fail(detail, DPIA_ERR_SHAPE, os.str());
+      return fail(detail, DPIA_ERR_SHAPE,
+                  text("m = ", m, " is not a multiple of rows_per_wg = ", q.R));
     }
     // rows shorter than W * row_parts are zero-extended (no partial
     // product of a missing element changes a fold from +0)
     if (k < 1 || k > q.W * q.row_parts) {
-      os << "k = " << k << " must be in [1, seq_len * local_size * row_parts = "
-         << q.W * q.row_parts << "]";
-      return fail(detail, DPIA_ERR_SHAPE, os.str());
+      return fail(detail, DPIA_ERR_SHAPE,
+                  text("k = ", k, " must be in [1, seq_len * local_size * row_parts = ",
+                       q.W * q.row_parts, "]"));
     }
     q.k = k;
     q.items = m;
@@ -162,16 +170,16 @@ dpia_status make_plan(const dpia_strategy* s, dpia_op op, dpia_dtype dt, int64_t
     // A length that is not a multiple of W is zero-extended to the next
     // multiple; that leaves plain folds unchanged but not compensated ones.
     if (n % q.W && compensated) {
-      os << "n = " << n << " is not a multiple of the chunk W = seq_len * local_size = " << q.W
-         << " (required for compensated accumulation)";
-      return fail(detail, DPIA_ERR_SHAPE, os.str());
+      return fail(detail, DPIA_ERR_SHAPE,
+                  text("n = ", n, " is not a multiple of the chunk W = seq_len * local_size = ",
+                       q.W, " (required for compensated accumulation)"));
     }
     q.n = n;
     q.items = (n + q.W - 1) / q.W;
   }
   if (q.W >= (int64_t(1) << 31)) {
-    os << "chunk W = seq_len * local_size = " << q.W << " must be below 2^31";
-    return fail(detail, DPIA_ERR_STRATEGY, os.str());
+    return fail(detail, DPIA_ERR_STRATEGY,
+                text("chunk W = seq_len * local_size = ", q.W, " must be below 2^31"));
   }
 
   // Vector width (semantics-free: it decides which lanes or elements one
@@ -189,13 +197,13 @@ dpia_status make_plan(const dpia_strategy* s, dpia_op op, dpia_dtype dt, int64_t
     q.team = static_cast<int>(q.L);
   }
   if (q.team > 1024) {
-    os << "one chunk would need " << q.team << " threads (> 1024); reduce local_size";
-    return fail(detail, DPIA_ERR_STRATEGY, os.str());
+    return fail(detail, DPIA_ERR_STRATEGY,
+                text("one chunk would need ", q.team, " threads (> 1024); reduce local_size"));
   }
   if (op == DPIA_OP_GEMV) {
     if (static_cast<int64_t>(q.team) * q.R > 1024) {
-      os << "rows_per_wg * threads per row = " << int64_t(q.team) * q.R << " > 1024";
-      return fail(detail, DPIA_ERR_STRATEGY, os.str());
+      return fail(detail, DPIA_ERR_STRATEGY,
+                  text("rows_per_wg * threads per row = ", int64_t(q.team) * q.R, " > 1024"));
     }
     int lg = 256 / (q.team * q.R);
     if (lg < 1) lg = 1;
@@ -277,8 +285,9 @@ dpia_status make_plan(const dpia_strategy* s, dpia_op op, dpia_dtype dt, int64_t
 #define DPIA_LDS_CAP (160 * 1024)   // gfx950: 160 KB of LDS per compute unit
 #endif
   if (lds > DPIA_LDS_CAP) {
-    os << "strategy needs " << lds << " bytes of LDS per work-group (> " << DPIA_LDS_CAP << ")";
-    return fail(detail, DPIA_ERR_STRATEGY, os.str());
+    return fail(detail, DPIA_ERR_STRATEGY,
+                text("strategy needs ", lds, " bytes of LDS per work-group (> ", DPIA_LDS_CAP,
+                     ")"));
   }
   q.lds_bytes = lds;
 
