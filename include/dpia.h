@@ -243,9 +243,9 @@ dpia_status dpia_gemv_blas(const dpia_strategy* s, dpia_dtype a_dt, int64_t m, i
 /*
  * y[i] = alpha * x[i] for i < n (the scal benchmark of Sec. 7.1; BLAS sscal
  * when y == x).  A map: each element is one binary32 product, whatever the
- * strategy, which only places elements on work-groups (chunks of W) and
- * lanes (C elements each, contiguous or strided); wg_combine, passes and
- * accum are ignored.  dt = DPIA_F32; x and y 16-byte aligned; y may equal x.
+ * strategy; which work-item makes it is free, and of the strategy (checked as
+ * for the other operations) only max_grid bears on the launch.  dt = DPIA_F32;
+ * x and y 16-byte aligned; y may equal x.
  */
 dpia_status dpia_scal(const dpia_strategy* s, dpia_dtype dt, int64_t n, float alpha,
                       const void* x, void* y, dpia_stream_t stream);

@@ -265,16 +265,10 @@ dpia_status make_plan(const dpia_strategy* s, dpia_op op, dpia_dtype dt, int64_t
     q.stage_off = round_up(lds, 16);
     lds = q.stage_off + static_cast<size_t>(q.wg_threads / 64) * stage_floats(64) * sizeof(float);
   }
-  if (op == DPIA_OP_SCAL) {
-    // a map: no combine and no fold; the contiguous order is staged through
-    // LDS per wavefront (one operand) under the same conditions as above
-    // in tiles of up to 64 elements of a row (whole rows when C allows)
-    q.stage = q.order == DPIA_ORDER_CONTIGUOUS && q.nv == 4 && q.C % 16 == 0 &&
-              q.wg_threads <= 256 && q.wg_threads % 64 == 0;
-    q.scal_tile = q.C % 64 == 0 ? 64 : (q.C % 32 == 0 ? 32 : 16);
+  if (op == DPIA_OP_SCAL) {   // a map: no combine, no fold, nothing staged
+    q.stage = false;
     q.stage_off = 0;
-    lds = q.stage ? static_cast<size_t>(q.wg_threads / 64) * 64 * (q.scal_tile + 4) * sizeof(float)
-                  : 0;
+    lds = 0;
   }
   if ((op == DPIA_OP_DOT || op == DPIA_OP_ASUM) && q.passes == 1) {
     // the last work-group of a 1-pass launch runs the final fold
