@@ -398,7 +398,14 @@ dpia_status batch_launch(const dpia_batch_plan* plan, void* ws, size_t ws_bytes,
   const int32_t* red = reinterpret_cast<const int32_t*>(base + plan->red_off);
   unsigned int* arrive = reinterpret_cast<unsigned int*>(base + plan->arrive_off);
   float* partials = reinterpret_cast<float*>(base + plan->part_off);
-  const int64_t cap = static_cast<int64_t>(device_cus()) * 8;
+  // Two launches: a work-group for every tile (up to 256 per compute unit), so
+  // that the hardware hands them out as work-groups end.  8 per compute unit
+  // that stride over the tiles were not all resident (5 are, at 92 registers),
+  // and the last three ran after the others (4,608 instances, 8 / 16 / 32 /
+  // 64 / 256 per compute unit and all: 2,053 / 1,963 / 1,895 / 1,877 / 1,862
+  // / 1,884 us).  One launch: persistent, since a work-group counts a tile
+  // while it works on the next.
+  const int64_t cap = static_cast<int64_t>(device_cus()) * (one_launch ? 8 : 256);
   const int grid = static_cast<int>(plan->ntiles < cap ? plan->ntiles : cap);
   int ntiles = plan->ntiles;
   hipError_t e;
