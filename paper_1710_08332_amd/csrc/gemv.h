@@ -34,10 +34,6 @@ struct GemvArgs {
 // per SIMD, so a batch's decodes, products and sums otherwise ran with no
 // loads of that SIMD in flight (measured at 16384^2, cache evicted, C=64
 // L=256: 53.1 -> 50.6-50.9 us; bf16 C=32 L=512 98.5 -> 97.3 us).
-#ifndef DPIA_ROW_BLOCK_PIPELINE
-#define DPIA_ROW_BLOCK_PIPELINE 1
-#endif
-
 template <class Op, int NV, int RB>
 __device__ __forceinline__ void row_block_folds(const Op& op, const int64_t (&row)[RB],
                                                 const bool (&act)[RB], int64_t lda, int64_t col0,
@@ -56,7 +52,6 @@ __device__ __forceinline__ void row_block_folds(const Op& op, const int64_t (&ro
   const int nfull = rows < C ? rows : C;
   const int start = t * NV;
   int k = 0;
-#if DPIA_ROW_BLOCK_PIPELINE
   if constexpr (U >= 2 && U % 2 == 0) {
     // two half batches: one in flight while the other is folded
     constexpr int H = U / 2;
@@ -101,7 +96,6 @@ __device__ __forceinline__ void row_block_folds(const Op& op, const int64_t (&ro
       }
     }
   }
-#endif
   for (; k + U <= nfull; k += U) {
     float xv[U][NV];
     typename Op::Code ca[U][RB][NV];   // codes: decoded only when folded
@@ -124,18 +118,34 @@ __device__ __forceinline__ void row_block_folds(const Op& op, const int64_t (&ro
           acc[b][v] = Op::step(typename Op::Term{av[v], xv[u][v]}, acc[b][v]);
       }
   }
-  for (; k < nfull; ++k) {
-    const int64_t c = col0 + start + static_cast<int64_t>(k) * L;
-    float xv[NV];
-    op.template load_x<NV>(c, xv);
+  // what is left (fewer than a half batch), in batches of 2 and 1 steps
+  auto some = [&](auto nc) {
+    constexpr int N = decltype(nc)::value;
+    float xv[N][NV];
+    typename Op::Code cc[N][RB][NV];
 #pragma unroll
-    for (int b = 0; b < RB; ++b) {
-      float av[NV];
-      op.template load_a<NV>(row[b], lda, c, av);
+    for (int u = 0; u < N; ++u) {
+      const int64_t c = col0 + start + static_cast<int64_t>(k + u) * L;
+      op.template load_x<NV>(c, xv[u]);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) acc[b][v] = Op::step(typename Op::Term{av[v], xv[v]}, acc[b][v]);
+      for (int b = 0; b < RB; ++b) op.template load_codes<NV>(row[b], lda, c, cc[u][b]);
     }
-  }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int b = 0; b < RB; ++b) {
+        float av[NV];
+        Op::template decode<NV>(cc[u][b], av);
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+          acc[b][v] = Op::step(typename Op::Term{av[v], xv[u][v]}, acc[b][v]);
+      }
+    k += N;
+  };
+  if constexpr (U > 2)
+    while (k + 2 <= nfull) some(ic<2>{});
+  while (k < nfull) some(ic<1>{});
   if (nfull < C) {   // the last, partly existing row of the part
     const int o = start + nfull * L;
     float xv[NV], av[RB][NV];
@@ -396,9 +406,52 @@ hipError_t launch_gemv_fed(const Plan& p, const Op& op, int64_t m, int64_t lda, 
   return nl == 4 ? by_combine(ic<4>{}) : (nl == 2 ? by_combine(ic<2>{}) : by_combine(ic<1>{}));
 }
 
+// bf16 / fp8 rows in the strided order, whole 16-byte loads per lane group:
+// RB rows per team at once, one wavefront's worth of teams per work-group.
+// Rows are independent, so the work-group's size is free; small ones leave no
+// compute unit idle while the last large ones end (measured at 16384^2, work-
+// groups of 256 and of 64 threads: bf16 C=32 L=512 with 4 rows 104.0 and 83.5
+// us, fp8 C=32 L=512 with 4 rows 58.9 and 45.5 us).
+template <class Op>
+bool gemv_blocks(const Plan& p) {
+  return p.order == DPIA_ORDER_STRIDED && p.team <= 256 &&
+         p.nv == kVecBytes / static_cast<int>(sizeof(typename Op::Code));
+}
+
+template <class Op, int RB>
+hipError_t launch_gemv_block(const Plan& p, const Op& op, int64_t m, int64_t lda,
+                             hipStream_t stream) {
+  constexpr int NV = kVecBytes / static_cast<int>(sizeof(typename Op::Code));
+  GemvArgs a{};
+  a.m = m;
+  a.k = p.k;
+  a.lda = lda;
+  a.W = static_cast<int>(p.W);
+  a.L = static_cast<int>(p.L);
+  a.C = static_cast<int>(p.C);
+  a.team = p.team;
+  // (never more teams than the plan's LDS is for: its work-groups hold at
+  // least 64 threads)
+  a.teams_per_wg = p.team < kWave ? kWave / p.team : 1;
+  if (a.teams_per_wg > p.teams_per_wg) a.teams_per_wg = p.teams_per_wg;
+  a.team_lds_elems = (p.combine == DPIA_COMBINE_SEQ) ? static_cast<int>(p.L)
+                                                     : (p.team > 64 ? p.team / 64 : 1);
+  a.parts = p.row_parts;
+  a.stage_off = -1;
+  const int64_t per_wg = static_cast<int64_t>(a.teams_per_wg) * RB;
+  const int64_t need = (m + per_wg - 1) / per_wg;
+  const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
+  const int64_t grid = need < cap ? need : cap;
+  auto kern = p.combine == DPIA_COMBINE_TREE ? gemv_block_kernel<Op, NV, kTree, RB>
+                                             : gemv_block_kernel<Op, NV, kSeq, RB>;
+  Op op_copy = op;
+  void* args[] = {&op_copy, &a};
+  return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
+                         dim3(a.teams_per_wg * p.team), args, p.lds_bytes, stream);
+}
+
 template <class Op, int MAXNV>
-hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipStream_t stream,
-                       int rb = 1) {
+hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipStream_t stream) {
   GemvArgs a{};
   a.m = m;
   a.k = p.k;
@@ -412,29 +465,6 @@ hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipS
                                                      : (p.team > 64 ? p.team / 64 : 1);
   a.parts = p.row_parts;
   a.stage_off = p.stage ? static_cast<int>(p.stage_off) : -1;
-  if constexpr (Op::kRowBlockable) {
-  if (rb > 1 && p.order == DPIA_ORDER_STRIDED && p.nv == MAXNV && p.wg_threads <= 256) {
-    // row blocking: each team reduces rb rows at once (see row_block_folds)
-    const int64_t per_wg = static_cast<int64_t>(p.teams_per_wg) * rb;
-    const int64_t need = (m + per_wg - 1) / per_wg;
-    const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid)
-                                   : static_cast<int64_t>(device_cus()) *
-                                         (2048 / p.wg_threads > 0 ? 2048 / p.wg_threads : 1);
-    const int64_t grid = need < cap ? need : cap;
-    auto go = [&](auto comb, auto rbc) {
-      constexpr int COMBINE = decltype(comb)::value;
-      constexpr int RB = decltype(rbc)::value;
-      auto kern = gemv_block_kernel<Op, MAXNV, COMBINE, RB>;
-      Op op_copy = op;
-      void* args[] = {&op_copy, &a};
-      return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
-                             dim3(p.wg_threads), args, p.lds_bytes, stream);
-    };
-    if (p.combine == DPIA_COMBINE_TREE)
-      return rb == 4 ? go(ic<0>{}, ic<4>{}) : go(ic<0>{}, ic<2>{});
-    return rb == 4 ? go(ic<1>{}, ic<4>{}) : go(ic<1>{}, ic<2>{});
-  }
-  }
   const int64_t grid = grid_size(p);
   return with_order_combine(p.order, p.combine, [&](auto ord, auto comb) {
     constexpr int ORDER = decltype(ord)::value;

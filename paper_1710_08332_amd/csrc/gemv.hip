@@ -5,17 +5,29 @@
 namespace dpia {
 
 extern template hipError_t launch_gemv<GemvF32, 4>(const Plan&, const GemvF32&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 extern template hipError_t launch_gemv<GemvF32Cached, 4>(const Plan&, const GemvF32Cached&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 extern template hipError_t launch_gemv<GemvBF16, 8>(const Plan&, const GemvBF16&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 extern template hipError_t launch_gemv<GemvFP8, 16>(const Plan&, const GemvFP8&, int64_t, int64_t,
-                                              hipStream_t, int);
-extern template hipError_t launch_gemv<GemvFP8Long, 16>(const Plan&, const GemvFP8Long&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 extern template hipError_t launch_gemv<GemvU32, 4>(const Plan&, const GemvU32&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
+extern template hipError_t launch_gemv_block<GemvBF16, 4>(const Plan&, const GemvBF16&, int64_t, int64_t,
+                                                 hipStream_t);
+extern template hipError_t launch_gemv_block<GemvBF16, 2>(const Plan&, const GemvBF16&, int64_t, int64_t,
+                                                 hipStream_t);
+extern template hipError_t launch_gemv_block<GemvBF16Deep, 1>(const Plan&, const GemvBF16Deep&, int64_t, int64_t,
+                                                 hipStream_t);
+extern template hipError_t launch_gemv_block<GemvFP8, 4>(const Plan&, const GemvFP8&, int64_t, int64_t,
+                                                 hipStream_t);
+extern template hipError_t launch_gemv_block<GemvFP8Deep, 4>(const Plan&, const GemvFP8Deep&, int64_t, int64_t,
+                                                 hipStream_t);
+extern template hipError_t launch_gemv_block<GemvFP8Deep, 2>(const Plan&, const GemvFP8Deep&, int64_t, int64_t,
+                                                 hipStream_t);
+extern template hipError_t launch_gemv_block<GemvFP8Deep, 1>(const Plan&, const GemvFP8Deep&, int64_t, int64_t,
+                                                 hipStream_t);
 extern template hipError_t launch_gemv_fed<GemvF32>(const Plan&, const GemvF32&, int64_t, int64_t, int,
                                              hipStream_t);
 
@@ -23,24 +35,47 @@ extern template hipError_t launch_gemv_fed<GemvF32>(const Plan&, const GemvF32&,
 
 using namespace dpia;
 
-#ifndef DPIA_ROW_BLOCK
-#define DPIA_ROW_BLOCK 2
-#endif
-// Rows one team reduces at once for bf16 / fp8 matrices (1 = no blocking):
-// with narrow A elements the x operand, reloaded per row, would otherwise
-// dominate the traffic through the vector caches.
-static constexpr int kRowBlock = DPIA_ROW_BLOCK;
+namespace {
 
-// fp8 rows: 4 rows per team where that still gives one or two work-groups
-// per compute unit, else 2.  Measured at 16384^2 (cache evicted), 4 rows
-// per team: C=64 L=256 66.0 -> 52.8 us, C=32 L=512 68.4 -> 58.8 us (256
-// and 512 work-groups); slower where it leaves 128 work-groups (C=128
-// L=128: 57.4 -> 67.9 us) or 1024 (C=16 L=1024: 58.6 -> 68.5 us).
-static int fp8_row_block(const Plan& p, int64_t m) {
-  const int64_t wgs4 = (m + int64_t(p.teams_per_wg) * 4 - 1) / (int64_t(p.teams_per_wg) * 4);
-  const int64_t cus = device_cus();
-  return (wgs4 >= cus && wgs4 <= 2 * cus) ? 4 : kRowBlock;
+// Row-blocked bf16 / fp8 rows.  More rows per team share each load of x;
+// fewer, with deeper batches, keep the memory busy when there are few
+// wavefronts.  `waves`: wavefronts of the launch with one row per team.
+// Measured with 64-thread work-groups (us; rows per team x elements per batch):
+//  bf16  16384^2 C=32 L=512 (16384 waves)    4x16 83.5  2x16 85.1  1x64 107.6
+//        16384 x 8192 C=32 L=256 (8192)      4x16 44.3  2x16 43.3  1x64 47.1
+//        4096 x 16384 C=32 L=512 (4096)      4x16 25.3  2x16 23.3  1x64 29.0
+//        4096 x 16384 C=64 L=256 (2048)      4x16 34.1  2x16 28.4  1x64 25.4
+//        1024 x 16384 C=512 L=32 (64)        4x16 211   2x16 177   1x64 62
+//  fp8   16384^2 C=32 L=512 (8192)    4x16 45.5  4x64 49.4  2x64 53.4  1x64 72.6
+//        16384^2 C=64 L=256 (4096)    4x16 63.8  4x64 49.2  2x64 49.0  1x64 72.8
+//        4096 x 16384 C=32 L=512 (2048)  4x16 29.7  4x64 19.3  2x64 15.5  1x64 23.1
+//        16384 x 8192 C=128 L=64 (1024)  4x16 113   4x64 59.6  2x64 44.3  1x64 41.1
+// (with 256-thread work-groups, 2 rows and 16 elements, the four bf16 rows
+// took 95.4, 53.2, 29.3 and 32.0 us, the fifth 192.)
+int64_t block_waves(const Plan& p, int64_t m) { return (m * p.team + kWave - 1) / kWave; }
+
+hipError_t launch_bf16(const Plan& p, const GemvBF16& op, int64_t m, int64_t lda, hipStream_t s) {
+  if (!gemv_blocks<GemvBF16>(p)) return launch_gemv<GemvBF16, 8>(p, op, m, lda, s);
+  const int64_t waves = block_waves(p, m), cus = device_cus();
+  if (waves >= 64 * cus) return launch_gemv_block<GemvBF16, 4>(p, op, m, lda, s);
+  if (waves >= 16 * cus) return launch_gemv_block<GemvBF16, 2>(p, op, m, lda, s);
+  const GemvBF16Deep deep{op.A, op.x, op.scale, op.y, op.blas, op.beta_zero, op.alpha, op.beta};
+  return launch_gemv_block<GemvBF16Deep, 1>(p, deep, m, lda, s);
 }
+
+hipError_t launch_fp8(const Plan& p, const GemvFP8& op, int64_t m, int64_t lda, hipStream_t s) {
+  if (!gemv_blocks<GemvFP8>(p)) return launch_gemv<GemvFP8, 16>(p, op, m, lda, s);
+  const int64_t waves = block_waves(p, m), cus = device_cus();
+  // (lanes shorter than 16 elements have no deep batch)
+  if (waves >= 32 * cus || (waves >= 16 * cus && p.C < 16))
+    return launch_gemv_block<GemvFP8, 4>(p, op, m, lda, s);
+  const GemvFP8Deep deep{op.A, op.x, op.scale, op.y, op.blas, op.beta_zero, op.alpha, op.beta};
+  if (waves >= 16 * cus) return launch_gemv_block<GemvFP8Deep, 4>(p, deep, m, lda, s);
+  if (waves >= 6 * cus) return launch_gemv_block<GemvFP8Deep, 2>(p, deep, m, lda, s);
+  return launch_gemv_block<GemvFP8Deep, 1>(p, deep, m, lda, s);
+}
+
+}  // namespace
 
 namespace {
 
@@ -97,25 +132,18 @@ dpia_status gemv_impl(const char* name, const dpia_strategy* s, dpia_dtype a_dt,
             m, lda, hs);
       break;
     case DPIA_BF16:
-      e = launch_gemv<GemvBF16, 8>(
-          p, with_epilogue(GemvBF16{static_cast<const uint16_t*>(A),
-                                    static_cast<const float*>(x), nullptr,
-                                    static_cast<float*>(y)}),
-          m, lda, hs, kRowBlock);
+      e = launch_bf16(p,
+                      with_epilogue(GemvBF16{static_cast<const uint16_t*>(A),
+                                             static_cast<const float*>(x), nullptr,
+                                             static_cast<float*>(y)}),
+                      m, lda, hs);
       break;
     case DPIA_FP8_E4M3:
-      if (p.C >= 64)
-        e = launch_gemv<GemvFP8Long, 16>(
-            p, with_epilogue(GemvFP8Long{static_cast<const uint8_t*>(A),
-                                         static_cast<const float*>(x), row_scale,
-                                         static_cast<float*>(y)}),
-            m, lda, hs, fp8_row_block(p, m));
-      else
-        e = launch_gemv<GemvFP8, 16>(
-            p, with_epilogue(GemvFP8{static_cast<const uint8_t*>(A),
-                                     static_cast<const float*>(x), row_scale,
-                                     static_cast<float*>(y)}),
-            m, lda, hs, fp8_row_block(p, m));
+      e = launch_fp8(p,
+                     with_epilogue(GemvFP8{static_cast<const uint8_t*>(A),
+                                           static_cast<const float*>(x), row_scale,
+                                           static_cast<float*>(y)}),
+                     m, lda, hs);
       break;
     case DPIA_I32:
       e = launch_gemv<GemvU32, 4>(

@@ -5,6 +5,6 @@
 namespace dpia {
 
 template hipError_t launch_gemv<GemvBF16, 8>(const Plan&, const GemvBF16&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 
 }  // namespace dpia

@@ -5,6 +5,6 @@
 namespace dpia {
 
 template hipError_t launch_gemv<GemvF32Cached, 4>(const Plan&, const GemvF32Cached&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 
 }  // namespace dpia

@@ -5,6 +5,6 @@
 namespace dpia {
 
 template hipError_t launch_gemv<GemvFP8, 16>(const Plan&, const GemvFP8&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 
 }  // namespace dpia

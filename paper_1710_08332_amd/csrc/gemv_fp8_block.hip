@@ -1,0 +1,16 @@
+// Row-blocked kernels of one matrix type (built apart from the others, so
+// that they build in parallel).
+#include "gemv.h"
+
+namespace dpia {
+
+template hipError_t launch_gemv_block<GemvFP8, 4>(const Plan&, const GemvFP8&, int64_t, int64_t,
+                                                 hipStream_t);
+template hipError_t launch_gemv_block<GemvFP8Deep, 4>(const Plan&, const GemvFP8Deep&, int64_t, int64_t,
+                                                 hipStream_t);
+template hipError_t launch_gemv_block<GemvFP8Deep, 2>(const Plan&, const GemvFP8Deep&, int64_t, int64_t,
+                                                 hipStream_t);
+template hipError_t launch_gemv_block<GemvFP8Deep, 1>(const Plan&, const GemvFP8Deep&, int64_t, int64_t,
+                                                 hipStream_t);
+
+}  // namespace dpia

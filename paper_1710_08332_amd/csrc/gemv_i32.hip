@@ -5,6 +5,6 @@
 namespace dpia {
 
 template hipError_t launch_gemv<GemvU32, 4>(const Plan&, const GemvU32&, int64_t, int64_t,
-                                              hipStream_t, int);
+                                              hipStream_t);
 
 }  // namespace dpia

@@ -259,7 +259,6 @@ struct GemvF32Acc {
       expand<NV>(r, z);
     }
   };
-  static constexpr bool kRowBlockable = true;
   // Row blocking: NV decoded elements of row `r` (part p, offset off), and
   // NV elements of x at the same offset, loaded separately so that one x
   // load can serve several rows.
@@ -341,12 +340,12 @@ using GemvF32 = GemvF32Acc<float, DecodeF32>;
 using GemvF32Cached = GemvF32Acc<float, DecodeF32, 0, 0>;
 using GemvBF16 = GemvF32Acc<uint16_t, DecodeBF16>;
 using GemvFP8 = GemvF32Acc<uint8_t, DecodeFP8>;
-// fp8 rows with long lanes: four 16-byte loads per row in flight (measured
-// faster from C = 64 up, slower for short lanes)
-using GemvFP8Long = GemvF32Acc<uint8_t, DecodeFP8, 64>;
+// deep batches: 8 (bf16) or 4 (fp8) 16-byte loads per row in flight, for the
+// row-blocked launches with few wavefronts (gemv.hip)
+using GemvBF16Deep = GemvF32Acc<uint16_t, DecodeBF16, 64>;
+using GemvFP8Deep = GemvF32Acc<uint8_t, DecodeFP8, 64>;
 
 struct GemvU32 {
-  static constexpr bool kRowBlockable = false;
   static constexpr bool kF32Rows = false;
   using Arith = PlainU32;
   using T = uint32_t;
