@@ -309,7 +309,7 @@ __device__ __forceinline__ typename A::T combine_lanes(typename A::T (&acc)[NL],
 // (register pressure lowered occupancy).
 template <int NV, int E = DPIA_BATCH_ELEMS>
 struct Batch {
-  static constexpr int U = (E / NV) < 1 ? 1 : ((E / NV) > 16 ? 16 : (E / NV));
+  static constexpr int U = (E / NV) < 1 ? 1 : ((E / NV) > 64 ? 64 : (E / NV));
 };
 
 // Elements per lane group that one batch of loads covers: operations may
@@ -435,6 +435,10 @@ __device__ __forceinline__ void lane_folds(const View& view, bool active, int t,
   if (__builtin_expect(nfull % U != 0, 0)) {
     int i = nb * U;
     asm("" : "+v"(from));
+    if constexpr (U > 32)
+      if (nfull & 32) batch(std::integral_constant<int, 32>{}, i), i += 32;
+    if constexpr (U > 16)
+      if (nfull & 16) batch(std::integral_constant<int, 16>{}, i), i += 16;
     if constexpr (U > 8)
       if (nfull & 8) batch(std::integral_constant<int, 8>{}, i), i += 8;
     if constexpr (U > 4)

@@ -323,8 +323,10 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
                            int out_f64, void* lds) {
   using T = typename A::T;
   constexpr int E = sizeof(T) > 4 ? 8 : 16;      // values per lane
-  // fewer values than this many lanes hold are folded lane by lane
-  constexpr int kFewLanes = 32;
+  // fewer values than this many lanes hold are folded lane by lane (a step of
+  // a pair's binary32 chain is ten instructions, not one)
+  constexpr bool kPairs = FINAL == kFinalKahan32 || FINAL == kFinalSum2_32;
+  constexpr int kFewLanes = kPairs ? 16 : 32;
   const int tid = static_cast<int>(threadIdx.x);
   int whole = static_cast<int>(blockDim.x) / kWave;   // wavefronts without missing threads
   whole = whole < kFoldWaves ? whole : kFoldWaves;
@@ -392,12 +394,11 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
           acc = walk_lanes<false>(v, acc, lanes, lane, start);
         } else {
           for (int l = 0; l < lanes; ++l) {
-            const int n = G - static_cast<int64_t>(l) * E < E
-                              ? static_cast<int>(G - static_cast<int64_t>(l) * E) : E;
+            // (a zero pair changes no pair that is finite, and one that is not
+            // has value NaN already)
             T a = acc;
 #pragma unroll
-            for (int j = 0; j < E; ++j)
-              if (j < n) a = A::add(v[j], a);
+            for (int j = 0; j < E; ++j) a = A::add(v[j], a);
             acc = T{lane_read(a.s, l), lane_read(a.c, l)};
           }
         }

@@ -72,12 +72,14 @@ struct DotU32 {
 // L=256 58.7% -> 67.1% of peak, C=256 L=512 81% -> 84.5%; with 1024 lanes the
 // default batch stays faster).
 struct DotF32Deep : DotF32 {
+  using Base = DotF32;
   static constexpr int kBatchElems = 2 * DPIA_BATCH_ELEMS;
 };
 // Four times the batch, for strategies with too few wavefronts to keep the
 // memory system busy otherwise (fewer than two per compute unit); staged
 // contiguous folds keep two tiles in flight.
 struct DotF32Deeper : DotF32 {
+  using Base = DotF32;
   static constexpr int kBatchElems = 4 * DPIA_BATCH_ELEMS;
   static constexpr int kStageDepth = 2;
 };
@@ -145,6 +147,21 @@ struct Sum2DotF32 {
   }
 };
 
+// Operation `Op` with batches of 64 elements per lane group, for launches of
+// few lanes (thin_plan, reduce.h); Base is the operation itself.
+template <class Op>
+struct Deep : Op {
+  static constexpr int kBatchElems = 4 * DPIA_BATCH_ELEMS;
+  using Base = Op;
+};
+template <class Op, class = void>
+struct BaseOp {
+  using type = Op;
+};
+template <class Op>
+struct BaseOp<Op, decltype(void(sizeof(typename Op::Base)))> {
+  using type = typename Op::Base;
+};
 
 // ---------------------------------------------------------------- gemv rows
 

@@ -42,6 +42,31 @@ struct ReduceArgs {
 
 // MAXT: the largest work-group it is launched with (256 or 1024); the
 // 256-thread build may use more registers than the 1024-thread one.
+// The arrival of a 1-pass work-group (one thread calls this, when all of the
+// work-group's chunk values are in memory): true for the last one of the
+// launch.  The counter is left at zero.
+__device__ __forceinline__ bool last_of(unsigned int* counter, unsigned count) {
+  if (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != count - 1)
+    return false;
+  __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
+// The same for launches of many work-groups.  Arrivals at one word are taken
+// one by one, about 9 ns each, and the work-groups of a launch end together;
+// so more than 256 of them count in kArriveGroups words, and the last of each
+// word in the first one (asum of 2^23, C=64 L=256, 512 work-groups 15.6 ->
+// 13.0 us; 256 work-groups would lose 0.7 us by the second step).  The words
+// fit the 256 bytes that a workspace keeps for them.
+constexpr unsigned kArriveGroups = 32;
+static_assert((1 + kArriveGroups) * sizeof(unsigned) <= kWsAlign, "the workspace's counters");
+__device__ __forceinline__ bool last_to_arrive(unsigned int* counter) {
+  if (gridDim.x <= 256) return last_of(counter, gridDim.x);
+  const unsigned g = blockIdx.x % kArriveGroups;
+  if (!last_of(counter + 1 + g, (gridDim.x - g + kArriveGroups - 1) / kArriveGroups)) return false;
+  return last_of(counter, kArriveGroups);
+}
+
 // STAGED: the contiguous order through LDS (see chunk_value).
 template <class Op, int ORDER, int NV, int COMBINE, int FINAL, int VEC, int MAXT, bool STAGED>
 __global__ void __launch_bounds__(MAXT) reduce_kernel(Op op, ReduceArgs a) {
@@ -84,15 +109,11 @@ __global__ void __launch_bounds__(MAXT) reduce_kernel(Op op, ReduceArgs a) {
     wait_memory();
     __syncthreads();
     if (threadIdx.x == 0) {
-      const unsigned prev =
-          __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      is_last = (prev == gridDim.x - 1);
+      is_last = last_to_arrive(a.counter);
     }
     __syncthreads();
     if (is_last) {
       final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds);
-      if (threadIdx.x == 0)   // leave the counter at zero for the next call
-        __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -190,15 +211,11 @@ __global__ void __launch_bounds__(kWave*(1 + kFedLoaders)) fed_reduce_kernel(Op 
     wait_memory();
     __syncthreads();
     if (threadIdx.x == 0) {
-      const unsigned prev =
-          __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      is_last = (prev == gridDim.x - 1);
+      is_last = last_of(a.counter, gridDim.x);
     }
     __syncthreads();
     if (is_last) {
       final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds);
-      if (threadIdx.x == 0)
-        __hip_atomic_store(a.counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
@@ -278,19 +295,22 @@ int fed_rows_strided(const Plan& p, bool can_split) {
   if (p.V != 1 || p.combine == DPIA_COMBINE_SEQ) return 0;
   if (p.L < 16 || p.L > 512 || (p.L & (p.L - 1)) || p.C % kFedStrideRows) return 0;
   const int64_t cus = device_cus();
-  if (p.items >= cus) return 0;
+  if (p.items > 2 * cus) return 0;
   const bool split = can_split && p.split_off;
   const int64_t ntiles = p.C / kFedStrideRows;
   auto fits = [&](int depth) { return ntiles >= depth && ntiles % depth == 0; };
-  auto ok = [&](int rows, int depth) {
+  auto ok = [&](int rows, int depth, int64_t most) {
     const int64_t per = p.L / rows;
-    if (rows > p.L || p.items * per > cus || !fits(depth)) return false;
+    if (rows > p.L || p.items * per > most || !fits(depth)) return false;
     if (p.combine == DPIA_COMBINE_TREE && per > 1 && (!split || per > kSplitMax)) return false;
     return true;
   };
-  if (ok(16, fed_depth<16, NOPS>())) return 16;
-  if (ok(32, fed_depth<32, NOPS>())) return 32;
-  if (ok(kWave, fed_depth<kWave, NOPS>())) return kWave;
+  // one work-group per compute unit, else two (what their LDS allows)
+  for (const int64_t most : {cus, 2 * cus}) {
+    if (ok(16, fed_depth<16, NOPS>(), most)) return 16;
+    if (ok(32, fed_depth<32, NOPS>(), most)) return 32;
+    if (ok(kWave, fed_depth<kWave, NOPS>(), most)) return kWave;
+  }
   return 0;
 }
 
@@ -316,6 +336,53 @@ int fed_rows(const Plan& p, bool can_split) {
     return 0;
   }
   return fits(fed_depth<kWave, NOPS>()) ? kWave : 0;
+}
+
+// The plan of a scalar strided launch with few lanes: one lane per thread (as
+// far as a chunk's lanes fit 256 threads), for the operations' deep batches.
+// A thread that holds 4 lanes brings 16 bytes per load, but there are a
+// quarter as many threads, each with only as many loads in flight as it has
+// registers.  What is in flight is lanes x batch: with one lane per thread a
+// batch is 64 steps of it.  Measured, 4 lanes and 1 per thread, each with its
+// best batch (us; lanes in the launch):
+//   dot  2^26 C=8192 L=16 (8,192)    735   221    asum 531 143
+//   dot  2^26 C=1024 L=64 (65,536)   97.5  90.8   asum 60.4 46.2
+//   dot  2^25 C=512 L=256 (65,536)   52.0  44.5   asum 34.2 25.5
+//   dot  2^23 C=256 L=64 (32,768)    26.6  16.8   asum 19.3 12.2
+//   dot  2^20 C=256 L=16 (4,096)     26.9  11.7   asum 21.1 9.3
+//   dot  2^25 C=256 L=16 (131,072)   67.4  70.3   asum 35.8 36.3
+//   dot  2^26 C=256 L=64 (262,144)   99.9  101    asum 50.7 47.9
+//   dot  2^26 C=64 L=64 (2^20)       127   116    asum 60.0 50.3
+// Hence up to 256 lanes per compute unit; an asum, with one operand to keep
+// in flight, also up to 512, and with a wavefront per chunk (L = 64) always.
+constexpr int kThinTeam = 256;
+inline bool thin_lanes(const Plan& p) {
+  if (p.order != DPIA_ORDER_STRIDED || p.V != 1 || p.nv == 1 || p.L > 4 * kThinTeam) return false;
+  const int64_t lanes = p.items * p.L, cus = device_cus();
+  if (p.op == DPIA_OP_ASUM) return p.L == kWave || lanes <= 512 * cus;
+  return lanes <= 256 * cus;
+}
+
+inline Plan thin_plan(const Plan& p) {
+  if (!thin_lanes(p)) return p;
+  Plan q = p;
+  q.nv = 1;
+  while (q.L / q.nv > kThinTeam && q.nv < p.nv) q.nv *= 2;
+  if (q.nv == p.nv) return p;
+  q.team = static_cast<int>(q.L / q.nv);
+  q.teams_per_wg = q.team >= kThinTeam ? 1 : kThinTeam / q.team;
+  while (q.teams_per_wg > 1 && (q.teams_per_wg / 2) * q.team >= kWave &&
+         (q.items + q.teams_per_wg - 1) / q.teams_per_wg < device_cus())
+    q.teams_per_wg /= 2;
+  q.wg_threads = q.teams_per_wg * q.team;
+  size_t lds = 0;
+  if (q.combine == DPIA_COMBINE_SEQ)
+    lds = static_cast<size_t>(q.teams_per_wg) * q.L * q.acc_bytes;
+  else if (q.combine == DPIA_COMBINE_TREE && q.team > kWave)
+    lds = static_cast<size_t>(q.teams_per_wg) * (q.team / kWave) * q.acc_bytes;
+  if (q.passes == 1 && lds < kFoldLds) lds = kFoldLds;
+  q.lds_bytes = (lds + 16 + 15) / 16 * 16;
+  return q;
 }
 
 template <class Op, int FINAL>
@@ -361,16 +428,14 @@ hipError_t launch_fed(const Plan& p, const Op& op, const ReduceArgs& a, int rows
 template <class Op, int FINAL>
 hipError_t launch_chunks(const Plan& p, const Op& op, const ReduceArgs& a, hipStream_t stream) {
   if (p.items == 0) return hipSuccess;
-  // (the loaders keep the tiles in flight, so the deeper load batches of
-  // DotF32Deep and DotF32Deeper would only add registers)
+  // (the loaders keep the tiles in flight, so deeper load batches would only
+  // add registers)
   const bool can_split = a.nodes != nullptr;
-  if constexpr (std::is_same<Op, DotF32Deeper>::value || std::is_same<Op, DotF32Deep>::value) {
-    if (const int rows = fed_rows<2>(p, can_split))
-      return launch_fed<DotF32, FINAL>(p, DotF32{op.x, op.y}, a, rows, stream);
-  } else if constexpr (Op::View::kStageable) {
+  using Fed = typename BaseOp<Op>::type;
+  if constexpr (Op::View::kStageable) {
     const int rows = fed_rows<Op::View::kOps>(p, can_split);
     if (rows && (FINAL == kFinalPlain || (p.V == 1 && p.combine == DPIA_COMBINE_TREE)))
-      return launch_fed<Op, FINAL>(p, op, a, rows, stream);
+      return launch_fed<Fed, FINAL>(p, static_cast<const Fed&>(op), a, rows, stream);
   }
   const int64_t grid = grid_size(p);
   return with_reduce_shape<FINAL == kFinalPlain>(p, [&](auto ord, auto comb, auto nvc, auto vec) {

@@ -51,19 +51,50 @@ extern template hipError_t launch_reduce<Sum2DotF32, kFinalSum2_64>(const Plan&,
 extern template hipError_t launch_chunks<Sum2DotF32, kFinalSum2_64>(const Plan&, const Sum2DotF32&, const ReduceArgs&,
                                                 hipStream_t);
 extern template hipError_t launch_fold<Sum2DotF32, kFinalSum2_64>(int64_t, const void*, void*, int, hipStream_t);
+extern template hipError_t launch_reduce<Deep<DotU32>, kFinalPlain>(const Plan&, const Deep<DotU32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+extern template hipError_t launch_chunks<Deep<DotU32>, kFinalPlain>(const Plan&, const Deep<DotU32>&, const ReduceArgs&,
+                                                hipStream_t);
+extern template hipError_t launch_fold<Deep<DotU32>, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
+extern template hipError_t launch_reduce<Deep<AsumF32>, kFinalPlain>(const Plan&, const Deep<AsumF32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+extern template hipError_t launch_chunks<Deep<AsumF32>, kFinalPlain>(const Plan&, const Deep<AsumF32>&, const ReduceArgs&,
+                                                hipStream_t);
+extern template hipError_t launch_fold<Deep<AsumF32>, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
+extern template hipError_t launch_reduce<Deep<KahanDotF32>, kFinalKahan32>(const Plan&, const Deep<KahanDotF32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+extern template hipError_t launch_chunks<Deep<KahanDotF32>, kFinalKahan32>(const Plan&, const Deep<KahanDotF32>&, const ReduceArgs&,
+                                                hipStream_t);
+extern template hipError_t launch_fold<Deep<KahanDotF32>, kFinalKahan32>(int64_t, const void*, void*, int, hipStream_t);
+extern template hipError_t launch_reduce<Deep<KahanDotF32>, kFinalKahan64>(const Plan&, const Deep<KahanDotF32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+extern template hipError_t launch_chunks<Deep<KahanDotF32>, kFinalKahan64>(const Plan&, const Deep<KahanDotF32>&, const ReduceArgs&,
+                                                hipStream_t);
+extern template hipError_t launch_fold<Deep<KahanDotF32>, kFinalKahan64>(int64_t, const void*, void*, int, hipStream_t);
+extern template hipError_t launch_reduce<Deep<Sum2DotF32>, kFinalSum2_32>(const Plan&, const Deep<Sum2DotF32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+extern template hipError_t launch_chunks<Deep<Sum2DotF32>, kFinalSum2_32>(const Plan&, const Deep<Sum2DotF32>&, const ReduceArgs&,
+                                                hipStream_t);
+extern template hipError_t launch_fold<Deep<Sum2DotF32>, kFinalSum2_32>(int64_t, const void*, void*, int, hipStream_t);
+extern template hipError_t launch_reduce<Deep<Sum2DotF32>, kFinalSum2_64>(const Plan&, const Deep<Sum2DotF32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+extern template hipError_t launch_chunks<Deep<Sum2DotF32>, kFinalSum2_64>(const Plan&, const Deep<Sum2DotF32>&, const ReduceArgs&,
+                                                hipStream_t);
+extern template hipError_t launch_fold<Deep<Sum2DotF32>, kFinalSum2_64>(int64_t, const void*, void*, int, hipStream_t);
 
 #ifndef DPIA_DEEPER_DOT
 #define DPIA_DEEPER_DOT 1
 #endif
 
-// Plain binary32 dots whose strided lanes form teams narrower than 1024
-// lanes use a deeper load batch: DotF32Deep, or DotF32Deeper when the whole
-// launch has fewer than two wavefronts per compute unit.  Contiguous dots
-// staged through LDS whose launch has fewer wavefronts than compute units
+// The load batch of a plain binary32 dot that is not thin (thin_plan): strided
+// lanes in teams narrower than 1024 lanes use DotF32Deep, or DotF32Deeper when
+// the whole launch has fewer than two wavefronts per compute unit.  Contiguous
+// dots staged through LDS whose launch has fewer wavefronts than compute units
 // use DotF32Deeper too (two staged tiles in flight); unstaged contiguous
 // dots keep the default batch (a deeper one would need 128 registers of
 // loads in flight).
 inline int dot_depth(const Plan& p) {
+  if (thin_lanes(p)) return 2;
   const int64_t waves = p.items * ((p.team + 63) / 64);
   const int64_t cus = device_cus();
   if (p.order != DPIA_ORDER_STRIDED)
@@ -72,33 +103,35 @@ inline int dot_depth(const Plan& p) {
   return (DPIA_DEEPER_DOT && waves < 2 * cus) ? 2 : 1;
 }
 
-// Calls f(op, final-kind constant) for the operation and accumulation of a plan.
+// Calls f(op, final-kind constant) for the operation, accumulation and load
+// batch of a plan.
 template <class F>
 hipError_t with_reduction(const Plan& p, const void* x, const void* y, F&& f) {
-  if (p.op == DPIA_OP_ASUM)
-    return f(AsumF32{static_cast<const float*>(x)}, ic<kFinalPlain>{});
+  const float* xf = static_cast<const float*>(x);
+  const float* yf = static_cast<const float*>(y);
+  const bool thin = thin_lanes(p);
+  // `op`, or the same with deep batches
+  auto at_depth = [&](auto op, auto fin) {
+    using Op = decltype(op);
+    if (thin) return f(Deep<Op>{op}, fin);
+    return f(op, fin);
+  };
+  if (p.op == DPIA_OP_ASUM) return at_depth(AsumF32{xf}, ic<kFinalPlain>{});
   if (p.dt == DPIA_I32)
-    return f(DotU32{static_cast<const uint32_t*>(x), static_cast<const uint32_t*>(y)},
-             ic<kFinalPlain>{});
+    return at_depth(DotU32{static_cast<const uint32_t*>(x), static_cast<const uint32_t*>(y)},
+                    ic<kFinalPlain>{});
   if (p.accum == DPIA_ACCUM_KAHAN) {
-    KahanDotF32 op{static_cast<const float*>(x), static_cast<const float*>(y)};
-    if (p.final_f64) return f(op, ic<kFinalKahan64>{});
-    return f(op, ic<kFinalKahan32>{});
+    if (p.final_f64) return at_depth(KahanDotF32{xf, yf}, ic<kFinalKahan64>{});
+    return at_depth(KahanDotF32{xf, yf}, ic<kFinalKahan32>{});
   }
   if (p.accum == DPIA_ACCUM_SUM2) {
-    Sum2DotF32 op{static_cast<const float*>(x), static_cast<const float*>(y)};
-    if (p.final_f64) return f(op, ic<kFinalSum2_64>{});
-    return f(op, ic<kFinalSum2_32>{});
+    if (p.final_f64) return at_depth(Sum2DotF32{xf, yf}, ic<kFinalSum2_64>{});
+    return at_depth(Sum2DotF32{xf, yf}, ic<kFinalSum2_32>{});
   }
   const int depth = dot_depth(p);
-  if (depth == 2)
-    return f(DotF32Deeper{{static_cast<const float*>(x), static_cast<const float*>(y)}},
-             ic<kFinalPlain>{});
-  if (depth == 1)
-    return f(DotF32Deep{{static_cast<const float*>(x), static_cast<const float*>(y)}},
-             ic<kFinalPlain>{});
-  return f(DotF32{static_cast<const float*>(x), static_cast<const float*>(y)},
-           ic<kFinalPlain>{});
+  if (depth == 2) return f(DotF32Deeper{{xf, yf}}, ic<kFinalPlain>{});
+  if (depth == 1) return f(DotF32Deep{{xf, yf}}, ic<kFinalPlain>{});
+  return f(DotF32{xf, yf}, ic<kFinalPlain>{});
 }
 
 namespace {
@@ -125,42 +158,15 @@ namespace {
 // Shared body of dpia_dot and dpia_dot_noalloc after validation: the launches
 // of a dot with its chunk values in `partials` and the 1-pass arrival
 // counter at `counter`.
-dpia_status dot_launch(const Plan& p, dpia_dtype dt, const void* x, const void* y, void* out,
+dpia_status dot_launch(const Plan& p, const void* x, const void* y, void* out,
                        dpia_dtype out_dt, void* partials, void* counter, hipStream_t hs,
                        const char* name, void* split = nullptr) {
-  hipError_t e;
-  if (dt == DPIA_I32) {
-    e = launch_reduce<DotU32, kFinalPlain>(
-        p, DotU32{static_cast<const uint32_t*>(x), static_cast<const uint32_t*>(y)}, out, 0,
-        partials, counter, hs, split);
-  } else if (p.accum == DPIA_ACCUM_KAHAN || p.accum == DPIA_ACCUM_SUM2) {
-    const float* xf = static_cast<const float*>(x);
-    const float* yf = static_cast<const float*>(y);
-    const int f64 = out_dt == DPIA_F64;
-    if (p.accum == DPIA_ACCUM_KAHAN) {
-      KahanDotF32 op{xf, yf};
-      e = p.final_f64 ? launch_reduce<KahanDotF32, kFinalKahan64>(p, op, out, f64, partials,
-                                                                  counter, hs, split)
-                      : launch_reduce<KahanDotF32, kFinalKahan32>(p, op, out, 0, partials,
-                                                                  counter, hs, split);
-    } else {
-      Sum2DotF32 op{xf, yf};
-      e = p.final_f64 ? launch_reduce<Sum2DotF32, kFinalSum2_64>(p, op, out, f64, partials,
-                                                                 counter, hs, split)
-                      : launch_reduce<Sum2DotF32, kFinalSum2_32>(p, op, out, 0, partials,
-                                                                 counter, hs, split);
-    }
-  } else {
-    const float* xf = static_cast<const float*>(x);
-    const float* yf = static_cast<const float*>(y);
-    const int depth = dot_depth(p);
-    e = depth == 2 ? launch_reduce<DotF32Deeper, kFinalPlain>(p, DotF32Deeper{{xf, yf}}, out, 0,
-                                                               partials, counter, hs, split)
-        : depth == 1 ? launch_reduce<DotF32Deep, kFinalPlain>(p, DotF32Deep{{xf, yf}}, out, 0,
-                                                              partials, counter, hs, split)
-                     : launch_reduce<DotF32, kFinalPlain>(p, DotF32{xf, yf}, out, 0, partials,
-                                                          counter, hs, split);
-  }
+  const int f64 = out_dt == DPIA_F64;
+  const Plan q = thin_plan(p);
+  hipError_t e = with_reduction(p, x, y, [&](auto op, auto fin) {
+    return launch_reduce<decltype(op), decltype(fin)::value>(q, op, out, f64, partials, counter, hs,
+                                                             split);
+  });
   if (e != hipSuccess) return hip_fail(e, name);
   clear_detail();
   return DPIA_OK;
@@ -197,7 +203,7 @@ extern "C" dpia_status dpia_dot(const dpia_strategy* s, dpia_dtype dt, int64_t n
   st = check_ws(p, ws, ws_bytes);
   if (st != DPIA_OK) return st;
   void* split = p.split_off ? static_cast<char*>(ws) + p.split_off : nullptr;
-  return dot_launch(p, dt, x, y, out, out_dt, ws, static_cast<char*>(ws) + p.partial_bytes,
+  return dot_launch(p, x, y, out, out_dt, ws, static_cast<char*>(ws) + p.partial_bytes,
                     reinterpret_cast<hipStream_t>(stream), "dpia_dot launch", split);
 }
 
@@ -268,7 +274,7 @@ extern "C" dpia_status dpia_dot_noalloc(const dpia_strategy* s, dpia_dtype dt, i
   st = scratch_for_current_device(hs, &base);
   if (st != DPIA_OK) return st;
   unsigned char* b = static_cast<unsigned char*>(base);
-  return dot_launch(p, dt, x, y, out, out_dt, b + kWsAlign, b, hs, "dpia_dot_noalloc launch");
+  return dot_launch(p, x, y, out, out_dt, b + kWsAlign, b, hs, "dpia_dot_noalloc launch");
 }
 
 extern "C" dpia_status dpia_asum(const dpia_strategy* s, dpia_dtype dt, int64_t n, const void* x,
@@ -284,10 +290,12 @@ extern "C" dpia_status dpia_asum(const dpia_strategy* s, dpia_dtype dt, int64_t 
   st = check_ws(p, ws, ws_bytes);
   if (st != DPIA_OK) return st;
   void* split = p.split_off ? static_cast<char*>(ws) + p.split_off : nullptr;
-  hipError_t e = launch_reduce<AsumF32, kFinalPlain>(p, AsumF32{static_cast<const float*>(x)},
-                                                     out, 0, ws,
-                                                     static_cast<char*>(ws) + p.partial_bytes,
-                                                     reinterpret_cast<hipStream_t>(stream), split);
+  const Plan q = thin_plan(p);
+  hipError_t e = with_reduction(p, x, nullptr, [&](auto op, auto fin) {
+    return launch_reduce<decltype(op), decltype(fin)::value>(
+        q, op, out, 0, ws, static_cast<char*>(ws) + p.partial_bytes,
+        reinterpret_cast<hipStream_t>(stream), split);
+  });
   if (e != hipSuccess) return hip_fail(e, "dpia_asum launch");
   clear_detail();
   return DPIA_OK;
@@ -316,8 +324,9 @@ extern "C" dpia_status dpia_chunks(const dpia_strategy* s, dpia_op op, dpia_dtyp
   hipError_t e = with_reduction(p, x, y, [&](auto op_v, auto fin) {
     using Op = decltype(op_v);
     constexpr int FINAL = decltype(fin)::value;
-    ReduceArgs a = reduce_args<Op>(p, chunks, nullptr, nullptr, 0, false);
-    return launch_chunks<Op, FINAL>(p, op_v, a, hs);
+    const Plan q = thin_plan(p);
+    ReduceArgs a = reduce_args<Op>(q, chunks, nullptr, nullptr, 0, false);
+    return launch_chunks<Op, FINAL>(q, op_v, a, hs);
   });
   if (e != hipSuccess) return hip_fail(e, "dpia_chunks launch");
   clear_detail();

@@ -4,6 +4,10 @@
 
 namespace dpia {
 
+// (fed kernels: reduce_asum_fed.hip)
+extern template hipError_t launch_fed<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, const ReduceArgs&, int,
+                                             hipStream_t);
+
 template hipError_t launch_reduce<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, void*, int, void*,
                                                 void*, hipStream_t, void*);
 template hipError_t launch_chunks<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, const ReduceArgs&,

@@ -1,0 +1,17 @@
+// Kernels and launches of one family of reductions (built apart from the
+// others, so that they build in parallel).
+#include "reduce.h"
+
+namespace dpia {
+
+// (fed kernels: reduce_asum_fed.hip)
+extern template hipError_t launch_fed<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, const ReduceArgs&, int,
+                                             hipStream_t);
+
+template hipError_t launch_reduce<Deep<AsumF32>, kFinalPlain>(const Plan&, const Deep<AsumF32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+template hipError_t launch_chunks<Deep<AsumF32>, kFinalPlain>(const Plan&, const Deep<AsumF32>&, const ReduceArgs&,
+                                                hipStream_t);
+template hipError_t launch_fold<Deep<AsumF32>, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
+
+}  // namespace dpia

@@ -4,6 +4,10 @@
 
 namespace dpia {
 
+// (fed kernels: reduce_dot_fed.hip)
+extern template hipError_t launch_fed<DotF32, kFinalPlain>(const Plan&, const DotF32&, const ReduceArgs&, int,
+                                             hipStream_t);
+
 template hipError_t launch_reduce<DotF32Deep, kFinalPlain>(const Plan&, const DotF32Deep&, void*, int, void*,
                                                 void*, hipStream_t, void*);
 template hipError_t launch_chunks<DotF32Deep, kFinalPlain>(const Plan&, const DotF32Deep&, const ReduceArgs&,

@@ -9,5 +9,10 @@ template hipError_t launch_reduce<DotU32, kFinalPlain>(const Plan&, const DotU32
 template hipError_t launch_chunks<DotU32, kFinalPlain>(const Plan&, const DotU32&, const ReduceArgs&,
                                                 hipStream_t);
 template hipError_t launch_fold<DotU32, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
+template hipError_t launch_reduce<Deep<DotU32>, kFinalPlain>(const Plan&, const Deep<DotU32>&, void*, int, void*,
+                                                void*, hipStream_t, void*);
+template hipError_t launch_chunks<Deep<DotU32>, kFinalPlain>(const Plan&, const Deep<DotU32>&, const ReduceArgs&,
+                                                hipStream_t);
+template hipError_t launch_fold<Deep<DotU32>, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
 
 }  // namespace dpia
