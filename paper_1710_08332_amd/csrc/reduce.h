@@ -18,6 +18,7 @@
 #include "fed.h"
 #include "fold.h"
 #include "ops.h"
+#include "rows.h"
 #include "host.h"
 #include "plan.h"
 
@@ -220,6 +221,74 @@ __global__ void __launch_bounds__(kWave*(1 + kFedLoaders)) fed_reduce_kernel(Op 
   }
 }
 
+// Contiguous lanes, ROWS to a wavefront (rows.h).  A work-group has 4
+// wavefronts; they take a chunk's groups of ROWS lanes in turn, or, where a
+// chunk has fewer than 4 such groups, 2 or 4 chunks at once (`teams_per_wg`).
+// LDS: the combine's scratch and later the fold's, the lane values at
+// kRowsScratch, the staging regions at `stage_off`.
+constexpr int kRowsWaves = 4;
+constexpr int kRowsScratch = 512;
+static_assert(kFoldLds <= kRowsScratch, "the fold's LDS");
+template <class Op, int COMBINE, int FINAL, int VEC, int ROWS, int D>
+__global__ void __launch_bounds__(kWave* kRowsWaves) rows_reduce_kernel(Op op, ReduceArgs a) {
+  using T = typename Op::T;
+  using A = typename Op::Arith;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  __shared__ int is_last;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+  const int per_chunk = kRowsWaves / a.teams_per_wg;   // wavefronts
+  const int chunk = wave / per_chunk;
+  const int t = static_cast<int>(threadIdx.x) - chunk * per_chunk * kWave;
+  T* scratch = reinterpret_cast<T*>(lds_raw);          // (used by single chunks only)
+  T* lanes = reinterpret_cast<T*>(lds_raw + kRowsScratch) + chunk * a.L * VEC;
+  float* stage = reinterpret_cast<float*>(lds_raw + a.stage_off) +
+                 wave * rows_stage_floats<ROWS>(Op::View::kOps);
+  T* partials = static_cast<T*>(a.partials);
+  const int slices = a.L / ROWS;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * a.teams_per_wg;
+  for (int64_t g0 = static_cast<int64_t>(blockIdx.x) * a.teams_per_wg; g0 < a.items;
+       g0 += stride) {
+    const int64_t g = g0 + chunk;
+    if (g < a.items) {
+      const auto view = op.chunk(g, a.W);
+      const int64_t rest = a.n - g * a.W;
+      const int limit = static_cast<int>(rest < a.W ? rest : a.W);
+      for (int s = wave - chunk * per_chunk; s < slices; s += per_chunk) {
+        T acc[VEC];
+        rows_fold<Op, VEC, ROWS, D>(view, s * ROWS, a.C * VEC, limit, stage, acc);
+        if (ROWS == kWave || lane < ROWS) {
+          const int l = s * ROWS + lane;
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) {
+            if constexpr (COMBINE == kNone)
+              store_coherent(partials + (g * a.L + l) * VEC + j, acc[j]);
+            else
+              lanes[j * a.L + l] = acc[j];
+          }
+        }
+      }
+    }
+    if constexpr (COMBINE != kNone) {
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) {
+        const T c = combine_stored<A, COMBINE>(lanes + j * a.L, a.L, t, per_chunk * kWave, scratch);
+        if (t == 0 && g < a.items) store_coherent(partials + g * VEC + j, c);
+      }
+      __syncthreads();   // the lane values may be written for the next chunk
+    }
+  }
+  if (a.one_pass) {
+    wait_memory();
+    __syncthreads();
+    if (threadIdx.x == 0) is_last = last_to_arrive(a.counter);
+    __syncthreads();
+    if (is_last)
+      final_fold<A, FINAL, true>(partials, a.values, a.out, a.out_f64, lds_raw);
+  }
+}
+
 template <class A, int FINAL>
 __global__ void __launch_bounds__(1024) final_kernel(const typename A::T* partials, int64_t G,
                                                      void* out, int out_f64) {
@@ -385,6 +454,76 @@ inline Plan thin_plan(const Plan& p) {
   return q;
 }
 
+// Lane rows per wavefront of a contiguous launch (0: contiguous_staged, 64
+// lanes to a wavefront and a thread for each of a chunk's lanes).  Measured,
+// that and with 16, 32 or 64 rows (us; lanes in the launch):
+//   dot  2^20 C=256 L=16 (4,096)      15.8  16: 10.7     asum 12.6 9.0
+//   dot  2^26 C=8192 L=16 (8,192)     339   16: 103      asum 242  73.6
+//   dot  2^26 C=4096 L=64 (16,384)    178   16: 92  32: 114   asum 129  54.9
+//   dot  2^25 C=1024 L=64 (32,768)    59.6  16: 52  32: 51.8  asum 41.8 35.9
+//   dot  2^25 C=512 L=64 (65,536)     52.8  16: 51  32: 48.4  asum 29.9 34.2, 28.1
+//   dot  2^23 C=64 L=64 (131,072)     22.2  16: 29.7 32: 23.8
+// Chunks of 128 or 256 lanes give every work-group 4 wavefronts of 64 rows
+// already; 32 rows help where two operands' rows are long, since a row is
+// then read 256 bytes at a time (2^25 C=1024 L=256 70.7 -> 57.4 us, 2^26
+// C=512 L=256 94 -> 86; asum 2^25 C=512 27.6 -> 30.6).  Longer teams had a
+// thread per lane without staging (2^26 C=128 L=1024 304 -> 85.5 us).
+inline int rows_per_wave(const Plan& p) {
+  if (p.order != DPIA_ORDER_CONTIGUOUS || p.dt != DPIA_F32 || p.nv != 4) return 0;
+  if ((p.V != 1 && p.V != 4) || (p.C * p.V) % 32) return 0;
+  const int64_t lanes = p.items * p.L, cus = device_cus();
+  if (p.L > 256) return p.L % kWave == 0 ? kWave : 0;
+  if (p.L > kWave)
+    return p.op == DPIA_OP_DOT && p.C * p.V >= 512 && p.L % 32 == 0 && lanes <= 512 * cus ? 32 : 0;
+  if (p.L != 16 && p.L != 32 && p.L != kWave) return 0;
+  if (lanes <= 128 * cus) return 16;
+  return p.L != 16 && lanes <= 256 * cus ? 32 : 0;
+}
+
+template <class Op, int FINAL>
+hipError_t launch_rows(const Plan& p, const Op& op, const ReduceArgs& a, int rows,
+                       hipStream_t stream) {
+  constexpr int NOPS = Op::View::kOps;
+  auto go = [&](auto comb, auto vec, auto nrows) {
+    constexpr int COMBINE = decltype(comb)::value;
+    constexpr int VEC = decltype(vec)::value;
+    constexpr int ROWS = decltype(nrows)::value;
+    // tiles in flight: a tile is 32 registers per operand
+    constexpr int D = ROWS == kWave ? 1 : (NOPS == 1 ? 4 : 2);
+    const int64_t slices = p.L / ROWS;
+    ReduceArgs a_copy = a;
+    a_copy.teams_per_wg = slices >= kRowsWaves ? 1 : kRowsWaves / static_cast<int>(slices);
+    a_copy.stage_off = kRowsScratch;
+    if (COMBINE != kNone)
+      a_copy.stage_off += static_cast<int>(
+          (a_copy.teams_per_wg * p.L * VEC * sizeof(typename Op::T) + 15) / 16 * 16);
+    const size_t lds = a_copy.stage_off + sizeof(float) * static_cast<size_t>(kRowsWaves) *
+                                              rows_stage_floats<ROWS>(NOPS);
+    const int64_t need = (p.items + a_copy.teams_per_wg - 1) / a_copy.teams_per_wg;
+    const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
+    const int64_t grid = need < cap ? need : cap;
+    Op op_copy = op;
+    void* args[] = {&op_copy, &a_copy};
+    auto kern = rows_reduce_kernel<Op, COMBINE, FINAL, VEC, ROWS, D>;
+    return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
+                           dim3(kWave * kRowsWaves), args, lds, stream);
+  };
+  auto by_rows = [&](auto comb, auto vec) {
+    if (rows == 16) return go(comb, vec, ic<16>{});
+    if (rows == 32) return go(comb, vec, ic<32>{});
+    return go(comb, vec, ic<kWave>{});
+  };
+  auto by_combine = [&](auto vec) {
+    if (p.combine == DPIA_COMBINE_TREE) return by_rows(ic<kTree>{}, vec);
+    if (p.combine == DPIA_COMBINE_SEQ) return by_rows(ic<kSeq>{}, vec);
+    if constexpr (FINAL == kFinalPlain) return by_rows(ic<kNone>{}, vec);
+    return hipErrorInvalidValue;
+  };
+  if constexpr (FINAL == kFinalPlain)
+    if (p.V == 4) return by_combine(ic<4>{});
+  return by_combine(ic<1>{});
+}
+
 template <class Op, int FINAL>
 hipError_t launch_fed(const Plan& p, const Op& op, const ReduceArgs& a, int rows,
                       hipStream_t stream) {
@@ -433,9 +572,16 @@ hipError_t launch_chunks(const Plan& p, const Op& op, const ReduceArgs& a, hipSt
   const bool can_split = a.nodes != nullptr;
   using Fed = typename BaseOp<Op>::type;
   if constexpr (Op::View::kStageable) {
+    // (loader wavefronts that take 64-lane chunks whole leave compute units
+    // idle: 3,000,000 elements, C=512 L=64: 27.4 us, 15.8 with 16 rows; Kahan's
+    // longer steps keep 64 lanes busy: 16.0 and 18.7 us at C=256)
+    const int per_wave = rows_per_wave(p);
     const int rows = fed_rows<Op::View::kOps>(p, can_split);
-    if (rows && (FINAL == kFinalPlain || (p.V == 1 && p.combine == DPIA_COMBINE_TREE)))
+    if (rows && !(rows == kWave && per_wave == 16 && FINAL == kFinalPlain) &&
+        (FINAL == kFinalPlain || (p.V == 1 && p.combine == DPIA_COMBINE_TREE)))
       return launch_fed<Fed, FINAL>(p, static_cast<const Fed&>(op), a, rows, stream);
+    if (per_wave)
+      return launch_rows<Fed, FINAL>(p, static_cast<const Fed&>(op), a, per_wave, stream);
   }
   const int64_t grid = grid_size(p);
   return with_reduce_shape<FINAL == kFinalPlain>(p, [&](auto ord, auto comb, auto nvc, auto vec) {

@@ -4,6 +4,8 @@
 
 namespace dpia {
 
+extern template hipError_t launch_rows<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, const ReduceArgs&, int,
+                                              hipStream_t);
 // (fed kernels: reduce_asum_fed.hip)
 extern template hipError_t launch_fed<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, const ReduceArgs&, int,
                                              hipStream_t);

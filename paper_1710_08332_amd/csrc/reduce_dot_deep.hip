@@ -4,6 +4,8 @@
 
 namespace dpia {
 
+extern template hipError_t launch_rows<DotF32, kFinalPlain>(const Plan&, const DotF32&, const ReduceArgs&, int,
+                                              hipStream_t);
 // (fed kernels: reduce_dot_fed.hip)
 extern template hipError_t launch_fed<DotF32, kFinalPlain>(const Plan&, const DotF32&, const ReduceArgs&, int,
                                              hipStream_t);

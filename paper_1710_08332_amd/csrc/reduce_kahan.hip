@@ -4,6 +4,10 @@
 
 namespace dpia {
 
+extern template hipError_t launch_rows<KahanDotF32, kFinalKahan64>(const Plan&, const KahanDotF32&, const ReduceArgs&, int,
+                                              hipStream_t);
+extern template hipError_t launch_rows<KahanDotF32, kFinalKahan32>(const Plan&, const KahanDotF32&, const ReduceArgs&, int,
+                                              hipStream_t);
 template hipError_t launch_reduce<KahanDotF32, kFinalKahan32>(const Plan&, const KahanDotF32&, void*, int, void*,
                                                 void*, hipStream_t, void*);
 template hipError_t launch_chunks<KahanDotF32, kFinalKahan32>(const Plan&, const KahanDotF32&, const ReduceArgs&,

@@ -4,6 +4,10 @@
 
 namespace dpia {
 
+extern template hipError_t launch_rows<Sum2DotF32, kFinalSum2_64>(const Plan&, const Sum2DotF32&, const ReduceArgs&, int,
+                                              hipStream_t);
+extern template hipError_t launch_rows<Sum2DotF32, kFinalSum2_32>(const Plan&, const Sum2DotF32&, const ReduceArgs&, int,
+                                              hipStream_t);
 template hipError_t launch_reduce<Sum2DotF32, kFinalSum2_32>(const Plan&, const Sum2DotF32&, void*, int, void*,
                                                 void*, hipStream_t, void*);
 template hipError_t launch_chunks<Sum2DotF32, kFinalSum2_32>(const Plan&, const Sum2DotF32&, const ReduceArgs&,
