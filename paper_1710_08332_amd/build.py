@@ -29,7 +29,7 @@ HIP_SOURCES = ["reduce_dot.hip", "reduce_dot_deep.hip", "reduce_dot_deeper.hip",
                "reduce_kahan.hip", "reduce_sum2.hip", "reduce_asum_deep.hip", "reduce_dot_fed.hip",
                "reduce_asum_fed.hip", "reduce_rows.hip", "reduce_rows_comp.hip", "reduce_i32.hip", "gemv_f32.hip",
                "gemv_f32_cached.hip", "gemv_fp8.hip", "gemv_fp8_block.hip", "gemv_bf16.hip",
-               "gemv_bf16_block.hip", "gemv_fed.hip", "gemv_i32.hip", "batch.hip", "map.hip", "reduce.hip", "gemv.hip",
+               "gemv_bf16_block.hip", "gemv_rows.hip", "gemv_fed.hip", "gemv_i32.hip", "batch.hip", "map.hip", "reduce.hip", "gemv.hip",
                "module.hip", "stream.hip"]
 CPP_SOURCES = ["plan.cpp"]
 

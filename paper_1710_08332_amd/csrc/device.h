@@ -540,6 +540,8 @@ __device__ __forceinline__ void contiguous_staged(const View& view, bool active,
   const int lane = threadIdx.x & (kWave - 1);
   int have = limit - t * C;                     // elements of this lane's row that exist
   have = active ? (have < 0 ? 0 : (have > C ? C : have)) : 0;
+  // no row of this wavefront exists (rows shorter than the strategy's lanes)
+  if (__ballot(have > 0) == 0) return;
   // this work-item loads part `part` of rows i * kStageRowsPerLoad + lane / kStageVec
   const int part = lane % kStageVec;
   const float* rowp[NOPS][kStageVec];
@@ -644,6 +646,7 @@ __device__ __forceinline__ void contiguous_staged_codes(const View& view, bool a
   const int lane = threadIdx.x & (kWave - 1);
   int have = limit - t * C;                     // elements of this lane's row that exist
   have = active ? (have < 0 ? 0 : (have > C ? C : have)) : 0;
+  if (__ballot(have > 0) == 0) return;          // no row of this wavefront exists
   const int pa = lane % PA, px = lane % PX;
   const E* rowa[PA];
   const float* rowx[PX];

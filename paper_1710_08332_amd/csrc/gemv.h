@@ -12,6 +12,7 @@
 #include "device.h"
 #include "fed.h"
 #include "ops.h"
+#include "rows.h"
 #include "host.h"
 #include "plan.h"
 
@@ -448,6 +449,129 @@ hipError_t launch_gemv_block(const Plan& p, const Op& op, int64_t m, int64_t lda
   void* args[] = {&op_copy, &a};
   return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
                          dim3(a.teams_per_wg * p.team), args, p.lds_bytes, stream);
+}
+
+// Contiguous binary32 rows, ROWS lane rows to a wavefront (rows.h):
+// `teams_per_wg` matrix rows to a work-group at once.
+template <class Op, int COMBINE, int ROWS, int D>
+__global__ void __launch_bounds__(kWave* kRowsWaves) gemv_rows_kernel(Op op, GemvArgs a) {
+  using T = typename Op::T;
+  using A = typename Op::Arith;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+  const int per_row = kRowsWaves / a.teams_per_wg;     // wavefronts
+  const int team = wave / per_row;
+  const int t = static_cast<int>(threadIdx.x) - team * per_row * kWave;
+  T* scratch = reinterpret_cast<T*>(lds_raw);          // (used by single rows only)
+  T* lanes = reinterpret_cast<T*>(lds_raw + kRowsScratch) + team * a.L;
+  float* stage = reinterpret_cast<float*>(lds_raw + a.stage_off) +
+                 wave * rows_stage_floats<ROWS>(Op::View::kOps);
+  const int slices = a.L / ROWS;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * a.teams_per_wg;
+  for (int64_t r0 = static_cast<int64_t>(blockIdx.x) * a.teams_per_wg; r0 < a.m; r0 += stride) {
+    const int64_t r = r0 + team;
+    auto part = [&](int p) {
+      const int64_t rest = a.k - static_cast<int64_t>(p) * a.W;
+      const int limit = static_cast<int>(rest < 0 ? 0 : (rest < a.W ? rest : a.W));
+      if (r < a.m) {
+        const auto view = op.part(r, p, a.lda, a.W);
+        for (int s = wave - team * per_row; s < slices; s += per_row) {
+          T acc[1];
+          rows_fold<Op, 1, ROWS, D, true>(view, s * ROWS, a.C, limit, stage, acc);
+          if (ROWS == kWave || lane < ROWS) lanes[s * ROWS + lane] = acc[0];
+        }
+      }
+      __syncthreads();
+      const T v = combine_stored<A, COMBINE>(lanes, a.L, t, per_row * kWave, scratch);
+      __syncthreads();   // the lane values may be written again
+      return v;
+    };
+    T v = part(0);
+    if (a.parts == 2) {
+      const T h1 = part(1);
+      v = tree_node<A>(v, h1);   // reduceSeq (+) 0 [h0, h1]
+    }
+    if (t == 0 && r < a.m) op.store(r, v);
+  }
+}
+
+// Lane rows per wavefront of contiguous binary32 rows (0: gemv_kernel), by the
+// same lines as a dot's chunks (rows_per_wave, reduce.h).  Measured, that and
+// this (us; m x k, lanes in the launch):
+//   256 x 16384  C=1024 L=16 (4,096)    39.4 17.7    C=32 L=512 13.6 7.3
+//   1024 x 16384 C=512 L=32 (32,768)    23.9 19.0    C=256 L=64 (65,536) 19.1 17.4
+//   1500 x 3001  C=192 L=16 (24,000)    14.8  9.9    C=32 L=512 17.8 11.4
+//   8192^2       C=32 L=512             160  77      16384^2 C=32 L=512 625 225
+// (8192 x 1000 under C=32 L=512, where 32 of a row's 512 lanes have elements,
+// 43 and 49 us: rows much shorter than their lanes stay with gemv_kernel.)
+inline int gemv_rows_per_wave(const Plan& p, int64_t m) {
+  if (p.order != DPIA_ORDER_CONTIGUOUS || p.nv != 4 || p.C % 32) return 0;
+  const int64_t lanes = m * p.L, cus = device_cus();
+  if (p.L > 256) return p.L % kWave == 0 && 8 * p.k >= p.W * p.row_parts ? kWave : 0;
+  if (p.L != 16 && p.L != 32 && p.L != kWave) return 0;
+  if (lanes <= 128 * cus) return 16;
+  return p.L != 16 && lanes <= 256 * cus ? 32 : 0;
+}
+
+template <class Op>
+hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda, int rows,
+                            hipStream_t stream) {
+  auto go = [&](auto comb, auto nrows) {
+    constexpr int COMBINE = decltype(comb)::value;
+    constexpr int ROWS = decltype(nrows)::value;
+    constexpr int D = ROWS == kWave ? 1 : 2;           // tiles in flight
+    const int64_t slices = p.L / ROWS;
+    GemvArgs a{};
+    a.m = m;
+    a.k = p.k;
+    a.lda = lda;
+    a.W = static_cast<int>(p.W);
+    a.L = static_cast<int>(p.L);
+    a.C = static_cast<int>(p.C);
+    a.parts = p.row_parts;
+    a.teams_per_wg = slices >= kRowsWaves ? 1 : kRowsWaves / static_cast<int>(slices);
+    a.stage_off = kRowsScratch +
+                  static_cast<int>((a.teams_per_wg * p.L * sizeof(typename Op::T) + 15) / 16 * 16);
+    const size_t lds = a.stage_off + sizeof(float) * static_cast<size_t>(kRowsWaves) *
+                                         rows_stage_floats<ROWS>(Op::View::kOps);
+    const int64_t need = (m + a.teams_per_wg - 1) / a.teams_per_wg;
+    const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
+    const int64_t grid = need < cap ? need : cap;
+    Op op_copy = op;
+    void* args[] = {&op_copy, &a};
+    auto kern = gemv_rows_kernel<Op, COMBINE, ROWS, D>;
+    return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
+                           dim3(kWave * kRowsWaves), args, lds, stream);
+  };
+  auto by_rows = [&](auto comb) {
+    if (rows == 16) return go(comb, ic<16>{});
+    if (rows == 32) return go(comb, ic<32>{});
+    return go(comb, ic<kWave>{});
+  };
+  return p.combine == DPIA_COMBINE_TREE ? by_rows(ic<kTree>{}) : by_rows(ic<kSeq>{});
+}
+
+// The plan of strided binary32 rows with few lanes in all: one lane per thread
+// with batches of 64 steps, as thin_plan (reduce.h) does for a dot.
+inline bool gemv_thin(const Plan& p, int64_t m) {
+  return p.order == DPIA_ORDER_STRIDED && p.nv == 4 && p.team >= 4 && p.L <= 256 &&
+         m * p.L <= 256 * static_cast<int64_t>(device_cus());
+}
+
+inline Plan gemv_thin_plan(const Plan& p, int64_t m) {
+  Plan q = p;
+  q.nv = 1;
+  q.team = static_cast<int>(q.L);
+  q.teams_per_wg = q.team >= 256 ? 1 : 256 / q.team;
+  while (q.teams_per_wg > 1 && (q.teams_per_wg / 2) * q.team >= kWave &&
+         (m + q.teams_per_wg - 1) / q.teams_per_wg < 4 * device_cus())
+    q.teams_per_wg /= 2;
+  q.wg_threads = q.teams_per_wg * q.team;
+  const size_t per_team = q.combine == DPIA_COMBINE_SEQ ? q.L : (q.team > kWave ? q.team / kWave : 1);
+  q.lds_bytes = (static_cast<size_t>(q.teams_per_wg) * per_team * sizeof(float) + 31) / 16 * 16;
+  q.stage = false;
+  return q;
 }
 
 template <class Op, int MAXNV>

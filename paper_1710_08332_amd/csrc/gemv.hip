@@ -12,6 +12,10 @@ extern template hipError_t launch_gemv<GemvBF16, 8>(const Plan&, const GemvBF16&
                                               hipStream_t);
 extern template hipError_t launch_gemv<GemvFP8, 16>(const Plan&, const GemvFP8&, int64_t, int64_t,
                                               hipStream_t);
+extern template hipError_t launch_gemv<GemvF32Deep, 4>(const Plan&, const GemvF32Deep&, int64_t, int64_t,
+                                              hipStream_t);
+extern template hipError_t launch_gemv_rows<GemvF32>(const Plan&, const GemvF32&, int64_t, int64_t, int,
+                                              hipStream_t);
 extern template hipError_t launch_gemv<GemvU32, 4>(const Plan&, const GemvU32&, int64_t, int64_t,
                                               hipStream_t);
 extern template hipError_t launch_gemv_block<GemvBF16, 4>(const Plan&, const GemvBF16&, int64_t, int64_t,
@@ -119,6 +123,17 @@ dpia_status gemv_impl(const char* name, const dpia_strategy* s, dpia_dtype a_dt,
             p, with_epilogue(GemvF32{static_cast<const float*>(A), static_cast<const float*>(x),
                                      nullptr, static_cast<float*>(y)}),
             m, lda, rows, hs);
+      else if (const int per_wave = gemv_rows_per_wave(p, m))
+        e = launch_gemv_rows(
+            p, with_epilogue(GemvF32{static_cast<const float*>(A), static_cast<const float*>(x),
+                                     nullptr, static_cast<float*>(y)}),
+            m, lda, per_wave, hs);
+      else if (gemv_thin(p, m))
+        e = launch_gemv<GemvF32Deep, 4>(
+            gemv_thin_plan(p, m),
+            with_epilogue(GemvF32Deep{static_cast<const float*>(A), static_cast<const float*>(x),
+                                      nullptr, static_cast<float*>(y)}),
+            m, lda, hs);
       else if (p.order == DPIA_ORDER_STRIDED && p.team < 4)
         e = launch_gemv<GemvF32Cached, 4>(
             p, with_epilogue(GemvF32Cached{static_cast<const float*>(A),

@@ -355,6 +355,8 @@ using GemvF32 = GemvF32Acc<float, DecodeF32>;
 // 16384^2: C=8192 L=2 1294 us cached, 3947 us non-temporal; C=1024 L=8 with
 // two row parts 252 against 524 us; teams of 4 and more gain or break even)
 using GemvF32Cached = GemvF32Acc<float, DecodeF32, 0, 0>;
+// 64 steps of one lane in flight, for launches of few lanes (gemv_thin_plan)
+using GemvF32Deep = GemvF32Acc<float, DecodeF32, 64>;
 using GemvBF16 = GemvF32Acc<uint16_t, DecodeBF16>;
 using GemvFP8 = GemvF32Acc<uint8_t, DecodeFP8>;
 // deep batches: 8 (bf16) or 4 (fp8) 16-byte loads per row in flight, for the

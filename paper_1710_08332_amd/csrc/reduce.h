@@ -221,14 +221,8 @@ __global__ void __launch_bounds__(kWave*(1 + kFedLoaders)) fed_reduce_kernel(Op 
   }
 }
 
-// Contiguous lanes, ROWS to a wavefront (rows.h).  A work-group has 4
-// wavefronts; they take a chunk's groups of ROWS lanes in turn, or, where a
-// chunk has fewer than 4 such groups, 2 or 4 chunks at once (`teams_per_wg`).
-// LDS: the combine's scratch and later the fold's, the lane values at
-// kRowsScratch, the staging regions at `stage_off`.
-constexpr int kRowsWaves = 4;
-constexpr int kRowsScratch = 512;
-static_assert(kFoldLds <= kRowsScratch, "the fold's LDS");
+// Contiguous lanes, ROWS to a wavefront (rows.h): `teams_per_wg` chunks to a
+// work-group at once, the staging regions at `stage_off`.
 template <class Op, int COMBINE, int FINAL, int VEC, int ROWS, int D>
 __global__ void __launch_bounds__(kWave* kRowsWaves) rows_reduce_kernel(Op op, ReduceArgs a) {
   using T = typename Op::T;

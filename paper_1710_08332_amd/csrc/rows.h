@@ -1,4 +1,4 @@
-// Contiguous lanes folded ROWS to a wavefront.
+// Contiguous lanes folded ROWS to a wavefront (dot, asum, binary32 gemv rows).
 //
 // contiguous_staged gives every thread of a wavefront a lane, so a wavefront
 // loads 64 rows 128 bytes at a time and a launch has a wavefront per 64 lanes.
@@ -25,11 +25,20 @@ constexpr int rows_tile() { return kTileElems / ROWS; }
 template <int ROWS>
 constexpr int rows_stage_floats(int nops) { return nops * ROWS * (rows_tile<ROWS>() + 4); }
 
+// A work-group has 4 wavefronts; they take a chunk's groups of ROWS lanes in
+// turn, or, where a chunk has fewer than 4 such groups, 2 or 4 chunks at once.
+// LDS: the combine's scratch (and, after the chunks, a 1-pass fold's) in the
+// first kRowsScratch bytes, the lane values, the staging regions.
+constexpr int kRowsWaves = 4;
+constexpr int kRowsScratch = 512;
+static_assert(kFoldLds <= kRowsScratch, "the fold's LDS");
+
 // Rows row0 .. row0 + ROWS - 1 of a chunk (Cel elements each, a multiple of
 // 32; `limit` elements of the chunk exist): lane r < ROWS folds row row0 + r
 // into acc, element e into component e % VEC.  `stage`: this wavefront's
-// rows_stage_floats.  D tiles in flight.
-template <class Op, int VEC, int ROWS, int D, class View>
+// rows_stage_floats.  D tiles in flight.  CACHED1: operand 1 is read with
+// cached loads (a gemv's x).
+template <class Op, int VEC, int ROWS, int D, bool CACHED1 = false, class View>
 __device__ __forceinline__ void rows_fold(const View& view, int row0, int Cel, int limit,
                                           float* stage, typename Op::T (&acc)[VEC]) {
   constexpr int NOPS = View::kOps;
@@ -41,12 +50,17 @@ __device__ __forceinline__ void rows_fold(const View& view, int row0, int Cel, i
   constexpr int SR = TE + 4;
 #pragma unroll
   for (int j = 0; j < VEC; ++j) acc[j] = Op::Arith::zero();
+  if (limit <= row0 * Cel) return;                     // none of the rows exists
   const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
   const int part = lane % PV, first = lane / PV;
   const int base = (row0 + first) * Cel + part * 4;    // (below W < 2^31)
   const int ntiles = (Cel + TE - 1) / TE;
   const bool whole = limit >= (row0 + ROWS) * Cel;     // every row exists
   f32x4 regs[D][NOPS][N];
+  auto load = [&](int o, int at) {
+    const f32x4* g = reinterpret_cast<const f32x4*>(view.operand(o) + at);
+    return CACHED1 && o == 1 ? ld<false>(g) : ld<DPIA_NT_LOADS != 0>(g);
+  };
   auto gload = [&](f32x4 (&rg)[NOPS][N], int tile) {
     const int e = tile * TE + part * 4;
     if (whole && (tile + 1) * TE <= Cel) {
@@ -54,8 +68,7 @@ __device__ __forceinline__ void rows_fold(const View& view, int row0, int Cel, i
       for (int o = 0; o < NOPS; ++o)
 #pragma unroll
         for (int i = 0; i < N; ++i)
-          rg[o][i] = ld<DPIA_NT_LOADS != 0>(reinterpret_cast<const f32x4*>(
-              view.operand(o) + (base + tile * TE + i * RPL * Cel)));
+          rg[o][i] = load(o, base + tile * TE + i * RPL * Cel);
     } else {
       // whole 16-byte parts that exist, zeros past them (which fold as the
       // identity: a chunk that is not whole is a plain operation's)
@@ -65,9 +78,7 @@ __device__ __forceinline__ void rows_fold(const View& view, int row0, int Cel, i
 #pragma unroll
         for (int o = 0; o < NOPS; ++o) {
           rg[o][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-          if (in)
-            rg[o][i] = ld<DPIA_NT_LOADS != 0>(reinterpret_cast<const f32x4*>(
-                view.operand(o) + (base + tile * TE + i * RPL * Cel)));
+          if (in) rg[o][i] = load(o, base + tile * TE + i * RPL * Cel);
         }
       }
     }
