@@ -14,6 +14,8 @@ extern template hipError_t launch_gemv<GemvFP8, 16>(const Plan&, const GemvFP8&,
                                               hipStream_t);
 extern template hipError_t launch_gemv<GemvF32Deep, 4>(const Plan&, const GemvF32Deep&, int64_t, int64_t,
                                               hipStream_t);
+extern template hipError_t launch_gemv_block<GemvF32, 1>(const Plan&, const GemvF32&, int64_t,
+                                                         int64_t, hipStream_t);
 extern template hipError_t launch_gemv_rows<GemvF32>(const Plan&, const GemvF32&, int64_t, int64_t, int,
                                               hipStream_t);
 extern template hipError_t launch_gemv<GemvU32, 4>(const Plan&, const GemvU32&, int64_t, int64_t,
@@ -40,6 +42,19 @@ extern template hipError_t launch_gemv_fed<GemvF32>(const Plan&, const GemvF32&,
 using namespace dpia;
 
 namespace {
+
+// Strided binary32 rows over 64 or 128 long lanes, in launches with wavefronts
+// enough: the row-blocked kernel with one row per team, whose batch is two
+// halves, one in flight while the other is folded.  A wavefront holds 4 or 2
+// such rows, so its loads cover 256 or 512 bytes of each, and gemv_kernel's
+// whole batches leave it without loads while it folds (us, before and now:
+// 8192^2 C=64 L=128 49.8, 42.4, C=128 L=64 46.7, 43.9; 16384^2 C=128 L=128
+// 168.6, 154.9, C=256 L=64 168.1, 162.7; but 8192^2 C=32 L=256 42.7, 44.2,
+// 16384^2 C=512 L=32 160.5, 166.6, 3432 x 15745 C=124 L=128 37.4, 38.5).
+bool gemv_halves(const Plan& p, int64_t m) {
+  return gemv_blocks<GemvF32>(p) && (p.L == 64 || p.L == 128) && p.C >= 64 &&
+         m * p.team >= 8 * kWave * static_cast<int64_t>(device_cus());
+}
 
 // Row-blocked bf16 / fp8 rows.  More rows per team share each load of x;
 // fewer, with deeper batches, keep the memory busy when there are few
@@ -133,6 +148,11 @@ dpia_status gemv_impl(const char* name, const dpia_strategy* s, dpia_dtype a_dt,
             gemv_thin_plan(p, m),
             with_epilogue(GemvF32Deep{static_cast<const float*>(A), static_cast<const float*>(x),
                                       nullptr, static_cast<float*>(y)}),
+            m, lda, hs);
+      else if (gemv_halves(p, m))
+        e = launch_gemv_block<GemvF32, 1>(
+            p, with_epilogue(GemvF32{static_cast<const float*>(A), static_cast<const float*>(x),
+                                     nullptr, static_cast<float*>(y)}),
             m, lda, hs);
       else if (p.order == DPIA_ORDER_STRIDED && p.team < 4)
         e = launch_gemv<GemvF32Cached, 4>(

@@ -58,3 +58,13 @@ def test_thin_strided_rows(L, C, parts):
                     max_grid=3 if C == 65 else 0)
     k = L * C * parts - L // 3
     check(29, k, s, -(-k // 4) * 4, blas=C == 63)
+
+
+# 8 wavefronts per compute unit: the batch in two halves from there on
+@pytest.mark.parametrize("L,m", ((64, 8191), (64, 8192), (128, 4095), (128, 4099)))
+@pytest.mark.parametrize("steps", (64, 66.5, 71))
+@pytest.mark.parametrize("combine", (dp.TREE, dp.SEQ))
+def test_half_batches(L, m, steps, combine):
+    k = int(L * steps)
+    s = dp.Strategy(seq_len=-(-k // L), local_size=L, order=dp.STRIDED, wg_combine=combine)
+    check(m, k, s, -(-k // 4) * 4, blas=steps == 71)
