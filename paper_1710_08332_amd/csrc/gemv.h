@@ -460,7 +460,8 @@ __global__ void __launch_bounds__(kWave* kRowsWaves) gemv_rows_kernel(Op op, Gem
   extern __shared__ __align__(16) unsigned char lds_raw[];
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
-  const int per_row = kRowsWaves / a.teams_per_wg;     // wavefronts
+  // wavefronts per row
+  const int per_row = static_cast<int>(blockDim.x) / kWave / a.teams_per_wg;
   const int team = wave / per_row;
   const int t = static_cast<int>(threadIdx.x) - team * per_row * kWave;
   T* scratch = reinterpret_cast<T*>(lds_raw);          // (used by single rows only)
@@ -530,10 +531,12 @@ hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda,
     a.L = static_cast<int>(p.L);
     a.C = static_cast<int>(p.C);
     a.parts = p.row_parts;
-    a.teams_per_wg = slices >= kRowsWaves ? 1 : kRowsWaves / static_cast<int>(slices);
+    a.teams_per_wg = rows_teams(slices, m, device_cus());
+    const int waves =
+        slices >= kRowsWaves ? kRowsWaves : a.teams_per_wg * static_cast<int>(slices);
     a.stage_off = kRowsScratch +
                   static_cast<int>((a.teams_per_wg * p.L * sizeof(typename Op::T) + 15) / 16 * 16);
-    const size_t lds = a.stage_off + sizeof(float) * static_cast<size_t>(kRowsWaves) *
+    const size_t lds = a.stage_off + sizeof(float) * static_cast<size_t>(waves) *
                                          rows_stage_floats<ROWS>(Op::View::kOps);
     const int64_t need = (m + a.teams_per_wg - 1) / a.teams_per_wg;
     const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
@@ -542,7 +545,7 @@ hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda,
     void* args[] = {&op_copy, &a};
     auto kern = gemv_rows_kernel<Op, COMBINE, ROWS, D>;
     return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
-                           dim3(kWave * kRowsWaves), args, lds, stream);
+                           dim3(kWave * waves), args, lds, stream);
   };
   auto by_rows = [&](auto comb) {
     if (rows == 16) return go(comb, ic<16>{});

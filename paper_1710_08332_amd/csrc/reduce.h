@@ -231,7 +231,8 @@ __global__ void __launch_bounds__(kWave* kRowsWaves) rows_reduce_kernel(Op op, R
   __shared__ int is_last;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
-  const int per_chunk = kRowsWaves / a.teams_per_wg;   // wavefronts
+  // wavefronts per chunk
+  const int per_chunk = static_cast<int>(blockDim.x) / kWave / a.teams_per_wg;
   const int chunk = wave / per_chunk;
   const int t = static_cast<int>(threadIdx.x) - chunk * per_chunk * kWave;
   T* scratch = reinterpret_cast<T*>(lds_raw);          // (used by single chunks only)
@@ -486,12 +487,14 @@ hipError_t launch_rows(const Plan& p, const Op& op, const ReduceArgs& a, int row
     constexpr int D = ROWS == kWave ? 1 : (NOPS == 1 ? 4 : 2);
     const int64_t slices = p.L / ROWS;
     ReduceArgs a_copy = a;
-    a_copy.teams_per_wg = slices >= kRowsWaves ? 1 : kRowsWaves / static_cast<int>(slices);
+    a_copy.teams_per_wg = rows_teams(slices, p.items, device_cus());
+    const int waves = slices >= kRowsWaves
+                          ? kRowsWaves : a_copy.teams_per_wg * static_cast<int>(slices);
     a_copy.stage_off = kRowsScratch;
     if (COMBINE != kNone)
       a_copy.stage_off += static_cast<int>(
           (a_copy.teams_per_wg * p.L * VEC * sizeof(typename Op::T) + 15) / 16 * 16);
-    const size_t lds = a_copy.stage_off + sizeof(float) * static_cast<size_t>(kRowsWaves) *
+    const size_t lds = a_copy.stage_off + sizeof(float) * static_cast<size_t>(waves) *
                                               rows_stage_floats<ROWS>(NOPS);
     const int64_t need = (p.items + a_copy.teams_per_wg - 1) / a_copy.teams_per_wg;
     const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
@@ -500,7 +503,7 @@ hipError_t launch_rows(const Plan& p, const Op& op, const ReduceArgs& a, int row
     void* args[] = {&op_copy, &a_copy};
     auto kern = rows_reduce_kernel<Op, COMBINE, FINAL, VEC, ROWS, D>;
     return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
-                           dim3(kWave * kRowsWaves), args, lds, stream);
+                           dim3(kWave * waves), args, lds, stream);
   };
   auto by_rows = [&](auto comb, auto vec) {
     if (rows == 16) return go(comb, vec, ic<16>{});

@@ -27,11 +27,20 @@ constexpr int rows_stage_floats(int nops) { return nops * ROWS * (rows_tile<ROWS
 
 // A work-group has 4 wavefronts; they take a chunk's groups of ROWS lanes in
 // turn, or, where a chunk has fewer than 4 such groups, 2 or 4 chunks at once.
+// (With fewer chunks than that gives every compute unit a work-group, fewer
+// chunks and wavefronts: rows_teams.)
 // LDS: the combine's scratch (and, after the chunks, a 1-pass fold's) in the
 // first kRowsScratch bytes, the lane values, the staging regions.
 constexpr int kRowsWaves = 4;
 constexpr int kRowsScratch = 512;
 static_assert(kFoldLds <= kRowsScratch, "the fold's LDS");
+
+// Chunks a work-group takes at once.
+inline int rows_teams(int64_t slices, int64_t items, int64_t cus) {
+  int teams = slices >= kRowsWaves ? 1 : kRowsWaves / static_cast<int>(slices);
+  while (teams > 1 && (items + teams - 1) / teams < cus) teams /= 2;
+  return teams;
+}
 
 // Rows row0 .. row0 + ROWS - 1 of a chunk (Cel elements each, a multiple of
 // 32; `limit` elements of the chunk exist): lane r < ROWS folds row row0 + r
