@@ -577,6 +577,25 @@ inline Plan gemv_thin_plan(const Plan& p, int64_t m) {
   return q;
 }
 
+// Whether staged contiguous teams are launched one wavefront's worth (or one
+// team) to a work-group instead of 256 threads.  Wavefronts that share a
+// work-group hold its 18 KB regions each until the slowest is done; alone they
+// come and go by themselves, which evens out the last round.  Measured, 256
+// threads and this (us):
+//   binary32  L=64  16384^2 C=256 185.5 180.5   16384 x 4096 C=64 56.2 54.8
+//             L=32  8192^2 C=256 50.7 49.2      16384^2 C=512 186 182
+//   bf16      L=64  16384 x 4096 C=64 47.8 43.8 4096^2 C=64 14.8 14.3
+//             L=128 8192^2 C=64 50.8 47.3       16384 x 4096 C=32 58.0 53.6
+//   fp8       L=64  16384 x 4096 C=64 38.4 34.8 8192^2 C=128 36.1 33.9
+// and where it does not: binary32 L=128 (16384^2 C=128 189.5 192.9, 8192 x
+// 1000 25.7 26.9), L=8 (16384^2 190.1 196.6); bf16 L=64 with longer lanes
+// (16384^2 C=256 148.8 150.5), L=16 and 32 (8192^2 C=256 L=32 40.0 40.8).
+inline bool gemv_by_wave(const Plan& p, bool f32) {
+  if (!p.stage || p.order != DPIA_ORDER_CONTIGUOUS) return false;
+  if (f32) return p.L == 32 || p.L == kWave;
+  return p.L == 2 * kWave || (p.L == kWave && p.C <= 128);
+}
+
 template <class Op, int MAXNV>
 hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipStream_t stream) {
   GemvArgs a{};
@@ -592,7 +611,17 @@ hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipS
                                                      : (p.team > 64 ? p.team / 64 : 1);
   a.parts = p.row_parts;
   a.stage_off = p.stage ? static_cast<int>(p.stage_off) : -1;
-  const int64_t grid = grid_size(p);
+  Plan q = p;
+  const int teams = p.team < kWave ? kWave / p.team : 1;
+  if (teams < p.teams_per_wg && p.nv == MAXNV && gemv_by_wave(p, Op::kF32Rows)) {
+    q.teams_per_wg = a.teams_per_wg = teams;
+    q.wg_threads = teams * p.team;
+    const size_t lanes = static_cast<size_t>(teams) * a.team_lds_elems * sizeof(typename Op::T);
+    a.stage_off = static_cast<int>((lanes + 15) / 16 * 16);
+    q.lds_bytes = a.stage_off +
+                  static_cast<size_t>(q.wg_threads / kWave) * stage_floats(kWave) * sizeof(float);
+  }
+  const int64_t grid = grid_size(q);
   return with_order_combine(p.order, p.combine, [&](auto ord, auto comb) {
     constexpr int ORDER = decltype(ord)::value;
     constexpr int COMBINE = decltype(comb)::value;
@@ -610,7 +639,7 @@ hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipS
       Op op_copy = op;
       void* args[] = {&op_copy, &a};
       return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
-                             dim3(p.wg_threads), args, p.lds_bytes, stream);
+                             dim3(q.wg_threads), args, q.lds_bytes, stream);
     });
   });
 }
