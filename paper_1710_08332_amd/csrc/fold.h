@@ -332,7 +332,13 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
   whole = whole < kFoldWaves ? whole : kFoldWaves;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  if constexpr (COHERENT) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  // only wavefronts that read values acquire them: with sixteen invalidates a
+  // 1-pass launch of 1024 threads with few chunks took 1.5 us longer (asum of
+  // 2,024,225, C=16 L=1024, in a graph: 11.1 -> 9.5 us)
+  const bool reads = std::is_integral_v<T> ? wave * kWave < G : wave == 0 || G > kFewLanes * E;
+  if constexpr (COHERENT) {
+    if (reads) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
   if constexpr (std::is_integral_v<T>) {
     // addition modulo 2^32 is associative: any order gives the same bits
     T* sums = static_cast<T*>(lds);
