@@ -364,9 +364,7 @@ hipError_t launch_gemv_fed(const Plan& p, const Op& op, int64_t m, int64_t lda, 
   a.parts = p.row_parts;
   a.stage_off = -1;
   const int nl = p.order == DPIA_ORDER_STRIDED ? p.nv : 1;
-  const int64_t need = m / a.teams_per_wg;
-  const int64_t grid = p.max_grid && need > static_cast<int64_t>(p.max_grid)
-                           ? static_cast<int64_t>(p.max_grid) : need;
+  const int64_t grid = bounded_grid(m / a.teams_per_wg, p.max_grid, kWave * (1 + kFedLoaders));
   const size_t lds = sizeof(float) * fed_ring_floats() +
                      sizeof(typename Op::T) * kWave * (1 + kFedLoaders) * 4;
   auto go = [&](auto nlc, auto comb, auto rc) {
@@ -440,9 +438,8 @@ hipError_t launch_gemv_block(const Plan& p, const Op& op, int64_t m, int64_t lda
   a.parts = p.row_parts;
   a.stage_off = -1;
   const int64_t per_wg = static_cast<int64_t>(a.teams_per_wg) * RB;
-  const int64_t need = (m + per_wg - 1) / per_wg;
-  const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
-  const int64_t grid = need < cap ? need : cap;
+  const int64_t grid =
+      bounded_grid((m + per_wg - 1) / per_wg, p.max_grid, a.teams_per_wg * p.team);
   auto kern = p.combine == DPIA_COMBINE_TREE ? gemv_block_kernel<Op, NV, kTree, RB>
                                              : gemv_block_kernel<Op, NV, kSeq, RB>;
   Op op_copy = op;
@@ -539,8 +536,7 @@ hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda,
     const size_t lds = a.stage_off + sizeof(float) * static_cast<size_t>(waves) *
                                          rows_stage_floats<ROWS>(Op::View::kOps);
     const int64_t need = (m + a.teams_per_wg - 1) / a.teams_per_wg;
-    const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
-    const int64_t grid = need < cap ? need : cap;
+    const int64_t grid = bounded_grid(need, p.max_grid, kWave * waves);
     Op op_copy = op;
     void* args[] = {&op_copy, &a};
     auto kern = gemv_rows_kernel<Op, COMBINE, ROWS, D>;

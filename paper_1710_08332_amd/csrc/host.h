@@ -27,16 +27,27 @@ inline int device_cus() {
   return cus;
 }
 
+// The grid of a kernel that strides over `need` work-groups' work: bounded by
+// the strategy's max_grid (0: it has none) and, since HIP takes fewer than
+// 2^32 work-items in a dimension of a launch, by the work-group's threads.
+inline int64_t bounded_grid(int64_t need, uint32_t max_grid, int64_t threads) {
+  const int64_t most = ((int64_t(1) << 32) - 1) / threads;
+  if (max_grid && need > static_cast<int64_t>(max_grid)) need = max_grid;
+  return need < most ? need : most;
+}
+
 // Work-groups to launch: one per group of `teams_per_wg` items, capped at
 // what the device keeps resident (or at the strategy's max_grid).  The
 // kernels distribute items by a grid-stride loop, so this never changes a
 // result.
 inline int64_t grid_size(const Plan& p) {
   int64_t need = (p.items + p.teams_per_wg - 1) / p.teams_per_wg;
-  int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid)
-                           : static_cast<int64_t>(device_cus()) *
-                                 (2048 / p.wg_threads > 0 ? 2048 / p.wg_threads : 1);
-  return need < cap ? need : cap;
+  if (!p.max_grid) {
+    const int64_t cap = static_cast<int64_t>(device_cus()) *
+                        (2048 / p.wg_threads > 0 ? 2048 / p.wg_threads : 1);
+    if (need > cap) need = cap;
+  }
+  return bounded_grid(need, p.max_grid, p.wg_threads);
 }
 
 inline bool aligned16(const void* ptr) {

@@ -56,9 +56,7 @@ extern "C" dpia_status dpia_scal(const dpia_strategy* s, dpia_dtype dt, int64_t 
   }
   // one work-group per 1,024 elements, or the strategy's bound on them
   constexpr int64_t kPer = kMapThreads * 4;
-  int64_t grid = (p.n + kPer - 1) / kPer;
-  const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
-  if (grid > cap) grid = cap;
+  const int64_t grid = bounded_grid((p.n + kPer - 1) / kPer, p.max_grid, kMapThreads);
   const float* xp = static_cast<const float*>(x);
   float* yp = static_cast<float*>(y);
   void* args[] = {&alpha, &xp, &yp, &p.n};

@@ -497,8 +497,7 @@ hipError_t launch_rows(const Plan& p, const Op& op, const ReduceArgs& a, int row
     const size_t lds = a_copy.stage_off + sizeof(float) * static_cast<size_t>(waves) *
                                               rows_stage_floats<ROWS>(NOPS);
     const int64_t need = (p.items + a_copy.teams_per_wg - 1) / a_copy.teams_per_wg;
-    const int64_t cap = p.max_grid ? static_cast<int64_t>(p.max_grid) : int64_t(1) << 30;
-    const int64_t grid = need < cap ? need : cap;
+    const int64_t grid = bounded_grid(need, p.max_grid, kWave * waves);
     Op op_copy = op;
     void* args[] = {&op_copy, &a_copy};
     auto kern = rows_reduce_kernel<Op, COMBINE, FINAL, VEC, ROWS, D>;
