@@ -17,8 +17,13 @@ from ._lib import (BF16, CONTIGUOUS, F32, F64, FP8_E4M3, I32, KAHAN, NONE, OP_AS
                    last_error_detail)
 
 
+class _Described:
+    """Room for a strategy's descriptor outside its fields' table (``vars``)."""
+    __slots__ = ("_c",)
+
+
 @dataclass(frozen=True)
-class Strategy:
+class Strategy(_Described):
     """Mirror of dpia_strategy (include/dpia.h)."""
     seq_len: int                  # C: elements folded sequentially per lane
     local_size: int               # L: lanes per chunk
@@ -40,14 +45,16 @@ class Strategy:
     def _ref(self):
         """A pointer to this strategy's descriptor, which is made once: the
         fields cannot change, and the library only reads it."""
-        r = self.__dict__.get("_c")
-        if r is None:
-            r = self.__dict__["_c"] = ctypes.pointer(self.c())
-        return r
+        try:
+            return self._c
+        except AttributeError:
+            r = ctypes.pointer(self.c())
+            object.__setattr__(self, "_c", r)
+            return r
 
     def __getstate__(self):
         # (copies and pickles hold the fields alone)
-        return {k: v for k, v in self.__dict__.items() if k != "_c"}
+        return self.__dict__.copy()
 
     def with_(self, **kw) -> "Strategy":
         return replace(self, **kw)

@@ -15,14 +15,17 @@ import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
+
 @functools.lru_cache(maxsize=None)
+
+
 def _recorder():
     out = os.path.join(tempfile.mkdtemp(prefix="dpia_launches_"), "recorder.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC",
                     os.path.join(HERE, "launch_recorder.cpp"), "-o", out, "-ldl"], check=True)
-
     atexit.register(shutil.rmtree, os.path.dirname(out), ignore_errors=True)
     return out
+
 
 def launches(calls):
     """``calls``: (entry point, strategy fields, other arguments by name); a
@@ -33,10 +36,12 @@ def launches(calls):
     assert r.returncode == 0, r.stderr[-2000:]
     return json.loads(r.stdout.splitlines()[-1])
 
+
 def _demangle(names):
     r = subprocess.run(["c++filt"], input="\n".join(names), capture_output=True, text=True,
                        check=True)
     return dict(zip(names, r.stdout.splitlines()))
+
 
 def _call(L, dp, entry, strategy, a):
     # made-up device addresses, 256-byte aligned and far apart
@@ -58,6 +63,7 @@ def _call(L, dp, entry, strategy, a):
     if entry == "fold":
         return L.dpia_fold(r, dp.OP_DOT, dt, a["n"], x, out, dp.I32 if dt == dp.I32 else dp.F32, None)
     raise ValueError(entry)
+
 
 def _main():
     rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)   # (before the library is loaded)

@@ -22,3 +22,14 @@ def test_descriptor_is_made_once_and_not_part_of_the_strategy():
     assert set(dataclasses.asdict(s)) == {f.name for f in dataclasses.fields(dp.Strategy)}
     t = s.with_(seq_len=32)
     assert t._ref().contents.seq_len == 32 and s._ref().contents.seq_len == 16
+
+
+def test_a_strategy_that_was_used_has_the_fields_of_one_that_was_not():
+    s = dp.Strategy(seq_len=16, local_size=64, order=dp.STRIDED, passes=1)
+    before = dict(vars(s))
+    dp.strategy_check(s, dp.OP_DOT, dp.F32, 0, 4096)
+    assert vars(s) == before
+    assert dp.Strategy(**vars(s)) == s
+    for t in (copy.copy(s), copy.deepcopy(s), pickle.loads(pickle.dumps(s))):
+        assert t == s and vars(t) == before
+        assert t._ref() is not s._ref()
