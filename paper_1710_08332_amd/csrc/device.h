@@ -307,11 +307,6 @@ __device__ __forceinline__ typename A::T combine_lanes(typename A::T (&acc)[NL],
 // consume the batch in increasing index order.  U * NV is kept near 16
 // elements per batch: a second, alternating batch was measured slower
 // (register pressure lowered occupancy).
-template <int NV, int E = DPIA_BATCH_ELEMS>
-struct Batch {
-  static constexpr int U = (E / NV) < 1 ? 1 : ((E / NV) > 64 ? 64 : (E / NV));
-};
-
 // Elements per lane group that one batch of loads covers: operations may
 // choose their own (Op::kBatchElems); the default is DPIA_BATCH_ELEMS.
 template <class Op, class = void>
@@ -321,6 +316,26 @@ struct OpBatch {
 template <class Op>
 struct OpBatch<Op, decltype(void(Op::kBatchElems))> {
   static constexpr int E = Op::kBatchElems;
+};
+// The most steps of a batch: 16, or what the operation says of strided lanes
+// (Op::kBatchSteps) and of contiguous ones (Op::kRowSteps).
+template <class Op, int ORDER, class = void>
+struct OpSteps {
+  static constexpr int most = 16;
+};
+template <class Op>
+struct OpSteps<Op, kStrided, decltype(void(Op::kBatchSteps))> {
+  static constexpr int most = Op::kBatchSteps;
+};
+template <class Op>
+struct OpSteps<Op, kContiguous, decltype(void(Op::kRowSteps))> {
+  static constexpr int most = Op::kRowSteps;
+};
+
+template <int NV, class Op, int ORDER>
+struct Batch {
+  static constexpr int E = OpBatch<Op>::E, most = OpSteps<Op, ORDER>::most;
+  static constexpr int U = (E / NV) < 1 ? 1 : ((E / NV) > most ? most : (E / NV));
 };
 
 // Views whose loads can be kept as loaded until the fold (kRaw: Raw<NV>,
@@ -344,7 +359,7 @@ __device__ __forceinline__ void lane_folds(const View& view, bool active, int t,
                                            int limit,
                                            typename Op::T (&acc)[ORDER == kStrided ? NV : 1]) {
   using Term = typename Op::Term;
-  constexpr int U = Batch<NV, OpBatch<Op>::E>::U;
+  constexpr int U = Batch<NV, Op, ORDER>::U;
   constexpr int NL = (ORDER == kStrided) ? NV : 1;
 #pragma unroll
   for (int v = 0; v < NL; ++v) acc[v] = Op::Arith::zero();

@@ -48,7 +48,7 @@ __device__ __forceinline__ void row_block_folds(const Op& op, const int64_t (&ro
 #pragma unroll
   for (int b = 0; b < RB; ++b) any = any || act[b];
   if (!any) return;
-  constexpr int U = Batch<NV, OpBatch<Op>::E>::U;
+  constexpr int U = Batch<NV, Op, kStrided>::U;
   const int rows = limit / L;
   const int nfull = rows < C ? rows : C;
   const int start = t * NV;

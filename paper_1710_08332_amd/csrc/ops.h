@@ -147,11 +147,12 @@ struct Sum2DotF32 {
   }
 };
 
-// Operation `Op` with batches of 64 elements per lane group, for launches of
-// few lanes (thin_plan, reduce.h); Base is the operation itself.
+// Operation `Op` with batches of 64 steps of a lane, for launches of few lanes
+// (thin_plan, reduce.h); Base is the operation itself.
 template <class Op>
 struct Deep : Op {
   static constexpr int kBatchElems = 4 * DPIA_BATCH_ELEMS;
+  static constexpr int kBatchSteps = 64;
   using Base = Op;
 };
 template <class Op, class = void>
@@ -228,6 +229,12 @@ struct GemvF32Acc {
       BATCH ? BATCH
             : (kF32 ? DPIA_F32_GEMV_BATCH_ELEMS
                     : (sizeof(E) == 2 ? DPIA_BF16_BATCH_ELEMS : DPIA_FP8_BATCH_ELEMS));
+  // The most steps of a batch where a load brings one element: 16, but 32 of
+  // contiguous binary32 lanes (512 x 4127 over 32 lanes of 129: 10.3 -> 8.4
+  // us; strided ones lose where there are many wavefronts, 4096^2 over 15
+  // lanes 22.3 -> 24.1), and 64 for GemvF32Deep (a BATCH of its own).
+  static constexpr int kBatchSteps = kF32 && BATCH ? BATCH : 16;
+  static constexpr int kRowSteps = kF32 ? kBatchElems : 16;
   static constexpr bool kStreamA = STREAM >= 0 ? STREAM != 0 : (!kF32 || DPIA_F32_GEMV_STREAM_A);
   struct View {
     static constexpr bool kStageable = std::is_same<E, float>::value;

@@ -6,81 +6,30 @@
 
 namespace dpia {
 
-extern template hipError_t launch_reduce<DotF32, kFinalPlain>(const Plan&, const DotF32&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<DotF32, kFinalPlain>(const Plan&, const DotF32&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<DotF32, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<DotF32Deep, kFinalPlain>(const Plan&, const DotF32Deep&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<DotF32Deep, kFinalPlain>(const Plan&, const DotF32Deep&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<DotF32Deep, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<DotF32Deeper, kFinalPlain>(const Plan&, const DotF32Deeper&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<DotF32Deeper, kFinalPlain>(const Plan&, const DotF32Deeper&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<DotF32Deeper, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<DotU32, kFinalPlain>(const Plan&, const DotU32&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<DotU32, kFinalPlain>(const Plan&, const DotU32&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<DotU32, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<AsumF32, kFinalPlain>(const Plan&, const AsumF32&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<AsumF32, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<KahanDotF32, kFinalKahan32>(const Plan&, const KahanDotF32&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<KahanDotF32, kFinalKahan32>(const Plan&, const KahanDotF32&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<KahanDotF32, kFinalKahan32>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<KahanDotF32, kFinalKahan64>(const Plan&, const KahanDotF32&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<KahanDotF32, kFinalKahan64>(const Plan&, const KahanDotF32&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<KahanDotF32, kFinalKahan64>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Sum2DotF32, kFinalSum2_32>(const Plan&, const Sum2DotF32&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Sum2DotF32, kFinalSum2_32>(const Plan&, const Sum2DotF32&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Sum2DotF32, kFinalSum2_32>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Sum2DotF32, kFinalSum2_64>(const Plan&, const Sum2DotF32&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Sum2DotF32, kFinalSum2_64>(const Plan&, const Sum2DotF32&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Sum2DotF32, kFinalSum2_64>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Deep<DotU32>, kFinalPlain>(const Plan&, const Deep<DotU32>&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Deep<DotU32>, kFinalPlain>(const Plan&, const Deep<DotU32>&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Deep<DotU32>, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Deep<AsumF32>, kFinalPlain>(const Plan&, const Deep<AsumF32>&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Deep<AsumF32>, kFinalPlain>(const Plan&, const Deep<AsumF32>&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Deep<AsumF32>, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Deep<KahanDotF32>, kFinalKahan32>(const Plan&, const Deep<KahanDotF32>&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Deep<KahanDotF32>, kFinalKahan32>(const Plan&, const Deep<KahanDotF32>&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Deep<KahanDotF32>, kFinalKahan32>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Deep<KahanDotF32>, kFinalKahan64>(const Plan&, const Deep<KahanDotF32>&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Deep<KahanDotF32>, kFinalKahan64>(const Plan&, const Deep<KahanDotF32>&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Deep<KahanDotF32>, kFinalKahan64>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Deep<Sum2DotF32>, kFinalSum2_32>(const Plan&, const Deep<Sum2DotF32>&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Deep<Sum2DotF32>, kFinalSum2_32>(const Plan&, const Deep<Sum2DotF32>&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Deep<Sum2DotF32>, kFinalSum2_32>(int64_t, const void*, void*, int, hipStream_t);
-extern template hipError_t launch_reduce<Deep<Sum2DotF32>, kFinalSum2_64>(const Plan&, const Deep<Sum2DotF32>&, void*, int, void*,
-                                                void*, hipStream_t, void*);
-extern template hipError_t launch_chunks<Deep<Sum2DotF32>, kFinalSum2_64>(const Plan&, const Deep<Sum2DotF32>&, const ReduceArgs&,
-                                                hipStream_t);
-extern template hipError_t launch_fold<Deep<Sum2DotF32>, kFinalSum2_64>(int64_t, const void*, void*, int, hipStream_t);
+// Kernels and launches of an operation (built in the files of its family).
+#define DPIA_EXTERN(OP, FINAL)                                                                  \
+  extern template hipError_t launch_reduce<OP, FINAL>(const Plan&, const OP&, void*, int, void*, \
+                                                      void*, hipStream_t, void*);               \
+  extern template hipError_t launch_chunks<OP, FINAL>(const Plan&, const OP&, const ReduceArgs&, \
+                                                      hipStream_t);                             \
+  extern template hipError_t launch_fold<OP, FINAL>(int64_t, const void*, void*, int, hipStream_t)
+DPIA_EXTERN(DotF32, kFinalPlain);
+DPIA_EXTERN(DotF32Deep, kFinalPlain);
+DPIA_EXTERN(DotF32Deeper, kFinalPlain);
+DPIA_EXTERN(DotU32, kFinalPlain);
+DPIA_EXTERN(AsumF32, kFinalPlain);
+DPIA_EXTERN(KahanDotF32, kFinalKahan32);
+DPIA_EXTERN(KahanDotF32, kFinalKahan64);
+DPIA_EXTERN(Sum2DotF32, kFinalSum2_32);
+DPIA_EXTERN(Sum2DotF32, kFinalSum2_64);
+DPIA_EXTERN(Deep<DotF32>, kFinalPlain);
+DPIA_EXTERN(Deep<DotU32>, kFinalPlain);
+DPIA_EXTERN(Deep<AsumF32>, kFinalPlain);
+DPIA_EXTERN(Deep<KahanDotF32>, kFinalKahan32);
+DPIA_EXTERN(Deep<KahanDotF32>, kFinalKahan64);
+DPIA_EXTERN(Deep<Sum2DotF32>, kFinalSum2_32);
+DPIA_EXTERN(Deep<Sum2DotF32>, kFinalSum2_64);
+#undef DPIA_EXTERN
 
 #ifndef DPIA_DEEPER_DOT
 #define DPIA_DEEPER_DOT 1
@@ -94,7 +43,6 @@ extern template hipError_t launch_fold<Deep<Sum2DotF32>, kFinalSum2_64>(int64_t,
 // dots keep the default batch (a deeper one would need 128 registers of
 // loads in flight).
 inline int dot_depth(const Plan& p) {
-  if (thin_lanes(p)) return 2;
   const int64_t waves = p.items * ((p.team + 63) / 64);
   const int64_t cus = device_cus();
   if (p.order != DPIA_ORDER_STRIDED)
@@ -128,6 +76,7 @@ hipError_t with_reduction(const Plan& p, const void* x, const void* y, F&& f) {
     if (p.final_f64) return at_depth(Sum2DotF32{xf, yf}, ic<kFinalSum2_64>{});
     return at_depth(Sum2DotF32{xf, yf}, ic<kFinalSum2_32>{});
   }
+  if (thin) return f(Deep<DotF32>{{xf, yf}}, ic<kFinalPlain>{});
   const int depth = dot_depth(p);
   if (depth == 2) return f(DotF32Deeper{{xf, yf}}, ic<kFinalPlain>{});
   if (depth == 1) return f(DotF32Deep{{xf, yf}}, ic<kFinalPlain>{});

@@ -15,5 +15,10 @@ template hipError_t launch_reduce<DotF32Deeper, kFinalPlain>(const Plan&, const 
 template hipError_t launch_chunks<DotF32Deeper, kFinalPlain>(const Plan&, const DotF32Deeper&, const ReduceArgs&,
                                                 hipStream_t);
 template hipError_t launch_fold<DotF32Deeper, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
+template hipError_t launch_reduce<Deep<DotF32>, kFinalPlain>(const Plan&, const Deep<DotF32>&, void*, int,
+                                                void*, void*, hipStream_t, void*);
+template hipError_t launch_chunks<Deep<DotF32>, kFinalPlain>(const Plan&, const Deep<DotF32>&,
+                                                const ReduceArgs&, hipStream_t);
+template hipError_t launch_fold<Deep<DotF32>, kFinalPlain>(int64_t, const void*, void*, int, hipStream_t);
 
 }  // namespace dpia

@@ -3,7 +3,7 @@ dimension of a launch, so a call of any size has to stay below that (the
 kernels stride over the rest)."""
 
 import paper_1710_08332_amd as dp
-from launches import launches
+from tests.launches import launches
 
 HUGE_GRID = (1 << 32) - 1     # a bound on the grid that bounds nothing
 
