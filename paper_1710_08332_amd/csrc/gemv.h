@@ -592,8 +592,7 @@ inline bool gemv_by_wave(const Plan& p, bool f32) {
   return p.L == 2 * kWave || (p.L == kWave && p.C <= 128);
 }
 
-template <class Op, int MAXNV>
-hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipStream_t stream) {
+inline GemvArgs gemv_args(const Plan& p, int64_t m, int64_t lda) {
   GemvArgs a{};
   a.m = m;
   a.k = p.k;
@@ -607,6 +606,25 @@ hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipS
                                                      : (p.team > 64 ? p.team / 64 : 1);
   a.parts = p.row_parts;
   a.stage_off = p.stage ? static_cast<int>(p.stage_off) : -1;
+  return a;
+}
+
+// A plan of gemv_thin_plan.
+template <class Op>
+hipError_t launch_gemv_thin(const Plan& p, const Op& op, int64_t m, int64_t lda,
+                            hipStream_t stream) {
+  GemvArgs a = gemv_args(p, m, lda);
+  auto kern = p.combine == DPIA_COMBINE_TREE ? gemv_kernel<Op, kStrided, 1, kTree, 256>
+                                             : gemv_kernel<Op, kStrided, 1, kSeq, 256>;
+  Op op_copy = op;
+  void* args[] = {&op_copy, &a};
+  return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid_size(p)),
+                         dim3(p.wg_threads), args, p.lds_bytes, stream);
+}
+
+template <class Op, int MAXNV>
+hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipStream_t stream) {
+  GemvArgs a = gemv_args(p, m, lda);
   Plan q = p;
   const int teams = p.team < kWave ? kWave / p.team : 1;
   if (teams < p.teams_per_wg && p.nv == MAXNV && gemv_by_wave(p, Op::kF32Rows)) {

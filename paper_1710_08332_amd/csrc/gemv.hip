@@ -12,7 +12,7 @@ extern template hipError_t launch_gemv<GemvBF16, 8>(const Plan&, const GemvBF16&
                                               hipStream_t);
 extern template hipError_t launch_gemv<GemvFP8, 16>(const Plan&, const GemvFP8&, int64_t, int64_t,
                                               hipStream_t);
-extern template hipError_t launch_gemv<GemvF32Deep, 4>(const Plan&, const GemvF32Deep&, int64_t, int64_t,
+extern template hipError_t launch_gemv_thin<GemvF32Deep>(const Plan&, const GemvF32Deep&, int64_t, int64_t,
                                               hipStream_t);
 extern template hipError_t launch_gemv_block<GemvF32, 1>(const Plan&, const GemvF32&, int64_t,
                                                          int64_t, hipStream_t);
@@ -144,7 +144,7 @@ dpia_status gemv_impl(const char* name, const dpia_strategy* s, dpia_dtype a_dt,
                                      nullptr, static_cast<float*>(y)}),
             m, lda, per_wave, hs);
       else if (gemv_thin(p, m))
-        e = launch_gemv<GemvF32Deep, 4>(
+        e = launch_gemv_thin<GemvF32Deep>(
             gemv_thin_plan(p, m),
             with_epilogue(GemvF32Deep{static_cast<const float*>(A), static_cast<const float*>(x),
                                       nullptr, static_cast<float*>(y)}),

@@ -8,7 +8,7 @@ template hipError_t launch_gemv_rows<GemvF32>(const Plan&, const GemvF32&, int64
                                               hipStream_t);
 template hipError_t launch_gemv_block<GemvF32, 1>(const Plan&, const GemvF32&, int64_t, int64_t,
                                                   hipStream_t);
-template hipError_t launch_gemv<GemvF32Deep, 4>(const Plan&, const GemvF32Deep&, int64_t, int64_t,
-                                                hipStream_t);
+template hipError_t launch_gemv_thin<GemvF32Deep>(const Plan&, const GemvF32Deep&, int64_t, int64_t,
+                                                  hipStream_t);
 
 }  // namespace dpia

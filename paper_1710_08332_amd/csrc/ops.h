@@ -155,6 +155,10 @@ struct Deep : Op {
   static constexpr int kBatchSteps = 64;
   using Base = Op;
 };
+template <class Op>
+constexpr bool is_deep = false;
+template <class Op>
+constexpr bool is_deep<Deep<Op>> = true;
 template <class Op, class = void>
 struct BaseOp {
   using type = Op;

@@ -342,6 +342,20 @@ hipError_t with_reduce_shape(const Plan& p, F&& f) {
   return hipErrorInvalidValue;
 }
 
+// The same for a plan of thin_lanes: strided scalar lanes in work-groups of at
+// most 256 threads.
+template <bool WIDE, class F>
+hipError_t with_thin_shape(const Plan& p, F&& f) {
+  if (p.order != DPIA_ORDER_STRIDED || p.V != 1 || p.wg_threads > 256)
+    return hipErrorInvalidValue;
+  return with_nv<4>(p.nv, [&](auto nvc) {
+    if (p.combine == DPIA_COMBINE_TREE) return f(ic<kStrided>{}, ic<kTree>{}, nvc, ic<1>{});
+    if (p.combine == DPIA_COMBINE_SEQ) return f(ic<kStrided>{}, ic<kSeq>{}, nvc, ic<1>{});
+    if constexpr (WIDE) return f(ic<kStrided>{}, ic<kNone>{}, nvc, ic<1>{});
+    return hipErrorInvalidValue;
+  });
+}
+
 // Lane rows per work-group when a plan's chunks are folded by
 // fed_reduce_kernel (0: they are not): staged contiguous lanes, one lane per
 // thread, fewer chunks than compute units (otherwise the launch has
@@ -588,14 +602,16 @@ hipError_t launch_chunks(const Plan& p, const Op& op, const ReduceArgs& a, hipSt
       return launch_rows<Fed, FINAL>(p, static_cast<const Fed&>(op), a, per_wave, stream);
   }
   const int64_t grid = grid_size(p);
-  return with_reduce_shape<FINAL == kFinalPlain>(p, [&](auto ord, auto comb, auto nvc, auto vec) {
+  auto go = [&](auto ord, auto comb, auto nvc, auto vec) {
     constexpr int ORDER = decltype(ord)::value;
     constexpr int COMBINE = decltype(comb)::value;
     constexpr int NV = decltype(nvc)::value;
     constexpr int VEC = decltype(vec)::value;
-    auto kern = p.wg_threads <= 256
-                    ? reduce_kernel<Op, ORDER, NV, COMBINE, FINAL, VEC, 256, false>
-                    : reduce_kernel<Op, ORDER, NV, COMBINE, FINAL, VEC, 1024, false>;
+    auto kern = reduce_kernel<Op, ORDER, NV, COMBINE, FINAL, VEC, 256, false>;
+    if constexpr (!is_deep<Op>) {
+      if (p.wg_threads > 256)
+        kern = reduce_kernel<Op, ORDER, NV, COMBINE, FINAL, VEC, 1024, false>;
+    }
     if constexpr (ORDER == kContiguous && NV == 4 && Op::View::kStageable) {
       if (p.stage) kern = reduce_kernel<Op, ORDER, NV, COMBINE, FINAL, VEC, 256, true>;
     }
@@ -604,7 +620,11 @@ hipError_t launch_chunks(const Plan& p, const Op& op, const ReduceArgs& a, hipSt
     void* args[] = {&op_copy, &a_copy};
     return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid), dim3(p.wg_threads),
                            args, p.lds_bytes, stream);
-  });
+  };
+  if constexpr (is_deep<Op>)
+    return with_thin_shape<FINAL == kFinalPlain>(p, go);
+  else
+    return with_reduce_shape<FINAL == kFinalPlain>(p, go);
 }
 
 // The outer reduceSeq over G chunk values, as a kernel of its own: 4

@@ -41,3 +41,23 @@ def test_few_strided_lanes_are_one_to_a_thread():
         if "fed_reduce_kernel" not in l["kernel"]:      # (loader wavefronts: few chunks)
             assert "Deep<" in l["kernel"] and f", 1, {nv}, " in l["kernel"], (call, l)
         assert l["block"] <= 320, (call, l)
+
+
+def test_every_build_for_few_lanes_can_be_launched():
+    # the library holds the deep batches' kernels for strided scalar lanes in
+    # teams of at most 256 threads only: order 1, 1, 2 or 4 lanes a thread, no vectors
+    import re
+    import subprocess
+    from paper_1710_08332_amd import _lib
+    names = subprocess.run(["nm", "-DC", "--defined-only", _lib.LIB_PATH], capture_output=True,
+                           text=True, check=True).stdout.splitlines()
+    deep = {m.group(1) for n in names
+            for m in [re.search(r"reduce_kernel<dpia::Deep<dpia::\w+>, ([^>]*)>", n)] if m}
+    assert deep
+    for shape in deep:
+        order, nv, _, _, vec, threads, staged = (v.strip() for v in shape.split(","))
+        assert (order, vec, threads, staged) == ("1", "1", "256", "false") and nv in "124", shape
+    rows = {m.group(1) for n in names
+            for m in [re.search(r"gemv_kernel<dpia::GemvF32Acc<float, dpia::DecodeF32, 64, -1>, ([^>]*)>", n)]
+            if m}
+    assert rows == {f"1, 1, {combine}, 256, false" for combine in (0, 1)}
