@@ -503,12 +503,23 @@ __global__ void __launch_bounds__(kWave* kRowsWaves) gemv_rows_kernel(Op op, Gem
 //   8192^2       C=32 L=512             160  77      16384^2 C=32 L=512 625 225
 // (8192 x 1000 under C=32 L=512, where 32 of a row's 512 lanes have elements,
 // 43 and 49 us: rows much shorter than their lanes stay with gemv_kernel.)
+// A row tile is 128 elements of 16 rows, so lanes shorter than 96 mostly load
+// nothing: rows win there only where the launch is small, or where the row's
+// length is no multiple of 4 and gemv_kernel's last parts are loaded one by one
+// (us, gemv_kernel and rows: 1024 x 512, C=32 L=16 3.4 4.2; 1024 x 2048, C=64
+// L=32 4.6 5.3; 256 x 2048, C=64 L=32 4.4 4.2; 256 x 131, C=32 L=16 5.9 4.2;
+// 256 x 2050, C=64 L=64 5.1 4.4; 256 x 1025, C=32 L=64 3.9 4.2).
+inline bool gemv_rows_short(const Plan& p, int64_t lanes, int64_t cus) {
+  const bool ragged = p.k % 4 != 0;
+  if (p.C >= 64) return (p.L < kWave && lanes <= 32 * cus) || (ragged && lanes <= 64 * cus);
+  return ragged && p.L < kWave && lanes <= 32 * cus;
+}
 inline int gemv_rows_per_wave(const Plan& p, int64_t m) {
   if (p.order != DPIA_ORDER_CONTIGUOUS || p.nv != 4 || p.C % 32) return 0;
   const int64_t lanes = m * p.L, cus = device_cus();
   if (p.L > 256) return p.L % kWave == 0 && 8 * p.k >= p.W * p.row_parts ? kWave : 0;
   if (p.L != 16 && p.L != 32 && p.L != kWave) return 0;
-  if (lanes <= 128 * cus) return 16;
+  if (lanes <= 128 * cus) return p.C >= 96 || gemv_rows_short(p, lanes, cus) ? 16 : 0;
   return p.L != 16 && lanes <= 256 * cus ? 32 : 0;
 }
 
@@ -552,10 +563,14 @@ hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda,
 }
 
 // The plan of strided binary32 rows with few lanes in all: one lane per thread
-// with batches of 64 steps, as thin_plan (reduce.h) does for a dot.
+// with batches of 64 steps, as thin_plan (reduce.h) does for a dot.  Shorter
+// lanes are in flight whole with four of them to a thread (us, that and one to
+// a thread: 1024 rows of L=64, C=8 2.5 3.4, C=16 3.4 3.8, C=24 4.3 4.5, C=32
+// 4.8 4.4, C=64 7.9 6.3; 64 rows of L=32, C=32 3.4 3.6, C=48 4.8 4.3).
 inline bool gemv_thin(const Plan& p, int64_t m) {
+  const int64_t lanes = m * p.L, cus = device_cus();
   return p.order == DPIA_ORDER_STRIDED && p.nv == 4 && p.team >= 4 && p.L <= 256 &&
-         m * p.L <= 256 * static_cast<int64_t>(device_cus());
+         lanes <= 256 * cus && p.C >= (lanes < 16 * cus ? 48 : 32);
 }
 
 inline Plan gemv_thin_plan(const Plan& p, int64_t m) {

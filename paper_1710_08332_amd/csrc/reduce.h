@@ -443,9 +443,27 @@ inline int thin_nv(const Plan& p) {
   while (p.L / nv > kThinTeam && nv < p.nv) nv *= 2;
   return p.L / nv > kThinTeam ? 0 : nv;
 }
+// Lanes so short that four of them to a thread have them in flight whole gain
+// nothing, and more threads cost (us; not thin and thin):
+//   asum 2^22 C=8 L=64    9.4 11.0   C=16 8.7  8.7
+//   dot  512 chunks of C=4 L=64 5.8 6.4   C=8 6.4 6.4
+// A 1-pass launch pays for every work-group's arrival besides (last_of), so
+// its lanes are one to a thread from 32 elements on (a dot with a last chunk in
+// part from 16: 8 chunks of C=16 L=64 4.8 us not thin, 4.0 thin; whole 3.6,
+// 3.7), and its work-groups hold 256 threads up to 64 (256 chunks of L=64, dot:
+// C=16 5.7 us not thin, 7.9 in work-groups of one wavefront, 5.8 in full ones;
+// C=32 7.2, 8.4, 6.7; C=64 8.9, 8.6, 7.4); where those are more than 256 then,
+// 512 chunks of C=32 L=256, an asum takes 10.9 us not thin, 11.4 thin.
+constexpr int kThinRound = 64;     // elements a lane has in flight at once
 inline bool thin_lanes(const Plan& p) {
   if (p.order != DPIA_ORDER_STRIDED || p.V != 1 || p.nv == 1 || !thin_nv(p)) return false;
   const int64_t lanes = p.items * p.L, cus = device_cus();
+  if (p.passes == 1) {
+    const bool part = p.op == DPIA_OP_DOT && p.n % p.W != 0;
+    if (p.C < (part ? 16 : 32) || (p.C < kThinRound && lanes > 256 * cus)) return false;
+  } else if (p.L >= kWave && p.C < (p.op == DPIA_OP_ASUM ? 16 : 8)) {
+    return false;
+  }
   if (p.op == DPIA_OP_ASUM) return p.L == kWave || lanes <= 512 * cus;
   return lanes <= 256 * cus;
 }
@@ -457,7 +475,8 @@ inline Plan thin_plan(const Plan& p) {
   if (q.nv == p.nv) return p;
   q.team = static_cast<int>(q.L / q.nv);
   q.teams_per_wg = q.team >= kThinTeam ? 1 : kThinTeam / q.team;
-  while (q.teams_per_wg > 1 && (q.teams_per_wg / 2) * q.team >= kWave &&
+  while ((q.passes == 2 || q.C >= kThinRound) && q.teams_per_wg > 1 &&
+         (q.teams_per_wg / 2) * q.team >= kWave &&
          (q.items + q.teams_per_wg - 1) / q.teams_per_wg < device_cus())
     q.teams_per_wg /= 2;
   q.wg_threads = q.teams_per_wg * q.team;
@@ -483,18 +502,35 @@ inline Plan thin_plan(const Plan& p) {
 // Chunks of 128 or 256 lanes give every work-group 4 wavefronts of 64 rows
 // already; 32 rows help where two operands' rows are long, since a row is
 // then read 256 bytes at a time (2^25 C=1024 L=256 70.7 -> 57.4 us, 2^26
-// C=512 L=256 94 -> 86; asum 2^25 C=512 27.6 -> 30.6).  Longer teams had a
-// thread per lane without staging (2^26 C=128 L=1024 304 -> 85.5 us).
+// C=512 L=256 94 -> 86; asum 2^25 C=512 27.6 -> 30.6), up to 512 lanes per
+// compute unit, 192 where the lanes are not whole wavefronts (L=96 C=512, 700
+// chunks: 51.3 us, 56.4 in rows).  Longer teams had a thread per lane without
+// staging (2^26 C=128 L=1024 304 -> 85.5 us).
+// A row tile is 128 elements of 16 rows or 64 of 32, whether or not a row has
+// them, so short lanes stay with contiguous_staged (us, that and rows):
+//   dot  256 chunks of L=16  C=32 6.0 6.9    C=64 7.5 7.3   C=96 8.3 7.5
+//   asum 256 chunks of L=32  C=32 5.7 6.9    C=64 6.4 6.8   C=96 7.5 7.4
+//   asum 1024 chunks of L=64 C=128 11.5 12.1 C=256 17.3 18.6 C=384 23.4 22.9
+//   dot  64 chunks of L=16   C=32 5.9 6.2    C=64 6.7 6.2
+// and the two-step arrival of a 1-pass launch of 512 work-groups costs what
+// rows gain below 256 elements (asum, 512 chunks of L=64: C=128 12.0 13.3,
+// C=256 16.1 16.1).
+inline int rows_min_elems(const Plan& p, int rows, int64_t lanes) {
+  if (rows == 32) return 384;
+  if (p.passes == 1 && p.items * (p.L / rows) >= 2 * kRowsWaves * device_cus()) return 256;
+  return p.op == DPIA_OP_DOT && lanes <= 8 * device_cus() ? 64 : 96;
+}
 inline int rows_per_wave(const Plan& p) {
   if (p.order != DPIA_ORDER_CONTIGUOUS || p.dt != DPIA_F32 || p.nv != 4) return 0;
   if ((p.V != 1 && p.V != 4) || (p.C * p.V) % 32) return 0;
   const int64_t lanes = p.items * p.L, cus = device_cus();
   if (p.L > 256) return p.L % kWave == 0 ? kWave : 0;
   if (p.L > kWave)
-    return p.op == DPIA_OP_DOT && p.C * p.V >= 512 && p.L % 32 == 0 && lanes <= 512 * cus ? 32 : 0;
+    return p.op == DPIA_OP_DOT && p.C * p.V >= 512 && p.L % 32 == 0 &&
+                   lanes <= (p.L % kWave ? 192 : 512) * cus ? 32 : 0;
   if (p.L != 16 && p.L != 32 && p.L != kWave) return 0;
-  if (lanes <= 128 * cus) return 16;
-  return p.L != 16 && lanes <= 256 * cus ? 32 : 0;
+  const int rows = lanes <= 128 * cus ? 16 : (p.L != 16 && lanes <= 256 * cus ? 32 : 0);
+  return rows && p.C * p.V >= rows_min_elems(p, rows, lanes) ? rows : 0;
 }
 
 template <class Op, int FINAL>
@@ -509,7 +545,7 @@ hipError_t launch_rows(const Plan& p, const Op& op, const ReduceArgs& a, int row
     constexpr int D = ROWS == kWave ? 1 : (NOPS == 1 ? 4 : 2);
     const int64_t slices = p.L / ROWS;
     ReduceArgs a_copy = a;
-    a_copy.teams_per_wg = rows_teams(slices, p.items, device_cus());
+    a_copy.teams_per_wg = rows_teams(slices, p.items, a.one_pass ? device_cus() / 4 : device_cus());
     const int waves = slices >= kRowsWaves
                           ? kRowsWaves : a_copy.teams_per_wg * static_cast<int>(slices);
     a_copy.stage_off = kRowsScratch;

@@ -61,3 +61,49 @@ def test_every_build_for_few_lanes_can_be_launched():
             for m in [re.search(r"gemv_kernel<dpia::GemvF32Acc<float, dpia::DecodeF32, 64, -1>, ([^>]*)>", n)]
             if m}
     assert rows == {f"1, 1, {combine}, 256, false" for combine in (0, 1)}
+
+
+def test_short_strided_lanes_keep_four_to_a_thread():
+    # the whole of a lane is in flight as it is; one lane a thread only adds
+    # work-groups, and their arrivals in one pass
+    G = dict(order=dp.STRIDED, wg_combine=dp.TREE)
+    short = [("gemv", dict(seq_len=C, local_size=L, **G), dict(m=m, k=C * L))
+             for m, L in ((64, 16), (256, 64), (1024, 64), (4096, 16)) for C in (4, 8, 16, 24)]
+    short += [("gemv", dict(seq_len=32, local_size=16, **G), dict(m=64, k=512))]
+    short += [(op, dict(seq_len=C, local_size=L, passes=1, **G), dict(n=C * L * n))
+              for op in ("dot", "asum") for C in (4, 8, 16) for L, n in ((16, 64), (64, 256), (256, 64))]
+    short += [("asum", dict(seq_len=8, local_size=64, passes=2, **G), dict(n=1 << 22)),
+              ("asum", dict(seq_len=32, local_size=256, passes=1, **G), dict(n=32 * 256 * 512))]
+    for call, l in first_kernels(short):
+        assert "Deep<" not in l["kernel"] and "float, dpia::DecodeF32, 64" not in l["kernel"], (call, l)
+    long = [("gemv", dict(seq_len=C, local_size=L, **G), dict(m=m, k=C * L))
+            for m, L, C in ((64, 16, 48), (256, 64, 32), (1024, 64, 64), (4096, 16, 32))]
+    for call, l in first_kernels(long):
+        assert "float, dpia::DecodeF32, 64" in l["kernel"], (call, l)
+
+
+def test_one_pass_launches_of_short_lanes_hold_256_threads():
+    # 256 chunks of 64 lanes: 64 work-groups to arrive, not 256
+    calls = [(op, dict(seq_len=32, local_size=64, order=dp.STRIDED, passes=p), dict(n=32 * 64 * 256))
+             for op in ("dot", "asum") for p in (1, 2)]
+    calls += [(op, dict(seq_len=128, local_size=16, order=dp.CONTIGUOUS, passes=p),
+               dict(n=128 * 16 * 256)) for op in ("dot", "asum") for p in (1, 2)]
+    for call, l in first_kernels(calls):
+        assert l["grid"] == (64 if call[1]["passes"] == 1 else 256), (call, l)
+
+
+def test_contiguous_lanes_shorter_than_a_row_tile_stay_staged():
+    C = dict(order=dp.CONTIGUOUS, wg_combine=dp.TREE)
+    staged = [("gemv", dict(seq_len=c, local_size=L, **C), dict(m=m, k=c * L))
+              for m, c, L in ((1024, 32, 16), (1024, 64, 32), (512, 64, 64), (64, 32, 64))]
+    staged += [(op, dict(seq_len=c, local_size=L, passes=p, **C), dict(n=c * L * n))
+               for op in ("dot", "asum") for p in (1, 2)
+               for c, L, n in ((32, 16, 256), (64, 32, 256), (64, 64, 512), (128, 64, 1000))]
+    for call, l in first_kernels(staged):
+        assert "rows" not in l["kernel"], (call, l)
+    rows = [("gemv", dict(seq_len=c, local_size=L, **C), dict(m=m, k=k, lda=-(-k // 4) * 4))
+            for m, c, L, k in ((1024, 96, 16, 1536), (256, 64, 32, 2048), (256, 32, 16, 131))]
+    rows += [(op, dict(seq_len=c, local_size=L, passes=2, **C), dict(n=c * L * n))
+             for op in ("dot", "asum") for c, L, n in ((96, 16, 256), (128, 32, 64), (384, 64, 1000))]
+    for call, l in first_kernels(rows):
+        assert "rows" in l["kernel"], (call, l)
