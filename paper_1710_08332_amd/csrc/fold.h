@@ -192,6 +192,20 @@ __device__ __forceinline__ F walk_lanes(const F (&v)[E], F cur, int lanes, int l
   return cur;
 }
 
+// Whether the wavefront holds values of both signs.
+template <class F, int E>
+__device__ __forceinline__ bool both_signs(const F (&v)[E]) {
+  using U = typename FoldBits<F>::U;
+  U any = 0, all = ~U(0);
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    any |= to_bits(v[j]);
+    all &= to_bits(v[j]);
+  }
+  constexpr int kSign = sizeof(F) * 8 - 1;
+  return __ballot((any >> kSign) != 0) != 0 && __ballot((all >> kSign) == 0) != 0;
+}
+
 // A wavefront with more changes of binade than this, or whose starts fail
 // step 5 more often than this, is folded lane by lane: a stop costs about 30
 // instructions, a lane of walk_lanes 20.
@@ -207,10 +221,10 @@ constexpr int kFoldSlots = 2 * kFoldWaves + 1;
 // values (w * 64 + l) * E ..., zeros past the `lanes` lanes (of the first
 // `waves` wavefronts) that hold any.  Every thread of the work-group calls
 // this; acc ends as the chain's value in all of them, and `start` as the
-// calling lane's start.
+// calling lane's start.  `only`: these are all values of the fold.
 template <bool START, class F, int E>
 __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, int waves,
-                                            F* slots, F& start) {
+                                            F* slots, F& start, bool only) {
   using U = typename FoldBits<F>::U;
   constexpr int kMant = FoldBits<F>::kMantissa;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
@@ -221,10 +235,16 @@ __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, 
   wait_memory();   // the values are here: no wait is left in the loops below
   // 1. approximate starts
   F incl = F(0), own = F(0);
+  bool in_turn = false;                          // lane by lane
   if (mine) {
-    own = fold_lane(v, F(0));
-    incl = wave_prefix(own);
-    if (lane == kWave - 1) slots[wave] = incl;
+    // (one wavefront's values are all there are, of both signs: few lanes keep
+    // their binade, and what comes before the walk would be in vain)
+    if constexpr (!START) in_turn = only && waves == 1 && both_signs(v);
+    if (!in_turn) {
+      own = fold_lane(v, F(0));
+      incl = wave_prefix(own);
+      if (lane == kWave - 1) slots[wave] = incl;
+    }
   }
   if (threadIdx.x == 0) *failed = 0;
   __syncthreads();
@@ -232,7 +252,6 @@ __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, 
   Displace<U> d{0, 0}, inc{0, 0}, exc{0, 0};
   unsigned long long bad = 0;
   int head = 0;
-  bool in_turn = false;                          // lane by lane
   auto scan = [&] {
     // the last restart at or before this lane: a lane behind a stop
     const unsigned long long heads = (bad << 1 | 1ull) & (~0ull >> (63 - lane));
@@ -241,7 +260,7 @@ __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, 
     exc = Displace<U>{dpp<kWaveShr1>(U(0), inc.d0), dpp<kWaveShr1>(U(0), inc.d1)};
     if (lane == head) exc = Displace<U>{0, 0};
   };
-  if (mine) {
+  if (mine && !in_turn) {
     F p = acc;
     for (int w = 0; w < wave; ++w) p += slots[w];
     p += incl - own;
@@ -323,10 +342,8 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
                            int out_f64, void* lds) {
   using T = typename A::T;
   constexpr int E = sizeof(T) > 4 ? 8 : 16;      // values per lane
-  // fewer values than this many lanes hold are folded lane by lane (a step of
-  // a pair's binary32 chain is ten instructions, not one)
-  constexpr bool kPairs = FINAL == kFinalKahan32 || FINAL == kFinalSum2_32;
-  constexpr int kFewLanes = kPairs ? 16 : 32;
+  // fewer values than this many lanes hold are folded lane by lane
+  constexpr int kFewLanes = 32;
   const int tid = static_cast<int>(threadIdx.x);
   int whole = static_cast<int>(blockDim.x) / kWave;   // wavefronts without missing threads
   whole = whole < kFoldWaves ? whole : kFoldWaves;
@@ -411,6 +428,7 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
       }
     } else {
       const int64_t block = static_cast<int64_t>(whole) * kWave * E;
+      const bool only = G <= block;
       for (int64_t b = 0; b < G; b += block) {
         const int64_t left = G - b < block ? G - b : block;
         const int lanes = static_cast<int>((left + E - 1) / E);
@@ -421,10 +439,10 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
           double w[E], start;
 #pragma unroll
           for (int j = 0; j < E; ++j) w[j] = value64(v[j]);
-          block_chain<false>(w, acc64, lanes, waves, static_cast<double*>(lds), start);
+          block_chain<false>(w, acc64, lanes, waves, static_cast<double*>(lds), start, only);
         } else if constexpr (sizeof(T) == 4) {
           float start;
-          block_chain<false>(v, acc, lanes, waves, static_cast<float*>(lds), start);
+          block_chain<false>(v, acc, lanes, waves, static_cast<float*>(lds), start, only);
         } else {
           // pairs: the s parts are a chain of their own; from its running
           // values come the exact errors, and the c parts are a chain over
@@ -432,7 +450,7 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
           float s[E], w[2 * E], start = 0.0f, cstart;
 #pragma unroll
           for (int j = 0; j < E; ++j) s[j] = v[j].s;
-          block_chain<true>(s, acc.s, lanes, waves, static_cast<float*>(lds), start);
+          block_chain<true>(s, acc.s, lanes, waves, static_cast<float*>(lds), start, only);
           T l{start, 0.0f};
 #pragma unroll
           for (int j = 0; j < E; ++j) {
@@ -442,7 +460,7 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
             w[2 * j + 1] = j < n ? t.c : 0.0f;
             l = t;
           }
-          block_chain<false>(w, acc.c, lanes, waves, static_cast<float*>(lds), cstart);
+          block_chain<false>(w, acc.c, lanes, waves, static_cast<float*>(lds), cstart, only);
         }
       }
     }
