@@ -217,6 +217,16 @@ constexpr int kFoldTries = 2;
 constexpr int kFoldWaves = 16;
 constexpr int kFoldSlots = 2 * kFoldWaves + 1;
 
+// The thread's index, as nothing that is known before the fold: what the fold
+// derives from it would be held in registers all through a kernel that folds
+// inside a loop (the one-launch batch: 135 registers, 3 wavefronts per SIMD,
+// not 94 and 5).
+__device__ __forceinline__ int fold_thread() {
+  int t = static_cast<int>(threadIdx.x);
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // The chain from `acc` over a block's values: lane l of wavefront w holds
 // values (w * 64 + l) * E ..., zeros past the `lanes` lanes (of the first
 // `waves` wavefronts) that hold any.  Every thread of the work-group calls
@@ -227,8 +237,9 @@ __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, 
                                             F* slots, F& start, bool only) {
   using U = typename FoldBits<F>::U;
   constexpr int kMant = FoldBits<F>::kMantissa;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
-  const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+  const int tid = fold_thread();
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int lane = tid & (kWave - 1);
   const bool mine = wave < waves;
   F* ends = slots + kFoldWaves;
   int* failed = reinterpret_cast<int*>(slots + 2 * kFoldWaves);
@@ -246,7 +257,7 @@ __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, 
       if (lane == kWave - 1) slots[wave] = incl;
     }
   }
-  if (threadIdx.x == 0) *failed = 0;
+  if (tid == 0) *failed = 0;
   __syncthreads();
   // 2. displacements, and the lanes without (bad); 3. their scan
   Displace<U> d{0, 0}, inc{0, 0}, exc{0, 0};
@@ -305,7 +316,7 @@ __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, 
         if (lane == 0) ends[w] = from_bits<F>(end);
       }
       __syncthreads();
-      if (w == 0 && threadIdx.x == 0) *failed = 0;
+      if (w == 0 && tid == 0) *failed = 0;
     }
     // 5. every lane's chain ends where its successor's starts
     if (mine && !in_turn) {
@@ -335,8 +346,12 @@ static_assert(kFoldSlots * sizeof(double) <= kFoldLds, "the plan reserves the fo
 // this (at least one whole wavefront; at most 16 take part).  `lds`:
 // kFoldLds bytes, 8-byte aligned.
 // COHERENT: the chunk values were written by other work-groups of the same
-// launch with store_coherent, which put them in memory; one agent-scope
-// acquire makes this compute unit's plain loads see them.
+// launch with store_coherent, which put them in memory.  Few are read with
+// load_coherent; where more are, one agent-scope acquire in every wavefront
+// that reads makes this compute unit's plain (wide) loads see them.  An acquire
+// invalidates the compute unit's cache, which the other work-groups there go on
+// using: with one for each of the 3,000 small folds of a one-launch batch it
+// took 36 us, not 24.
 template <class A, int FINAL, bool COHERENT = false>
 __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_t G, void* out,
                            int out_f64, void* lds) {
@@ -344,15 +359,13 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
   constexpr int E = sizeof(T) > 4 ? 8 : 16;      // values per lane
   // fewer values than this many lanes hold are folded lane by lane
   constexpr int kFewLanes = 32;
-  const int tid = static_cast<int>(threadIdx.x);
+  const int tid = fold_thread();
   int whole = static_cast<int>(blockDim.x) / kWave;   // wavefronts without missing threads
   whole = whole < kFoldWaves ? whole : kFoldWaves;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  // only wavefronts that read values acquire them: with sixteen invalidates a
-  // 1-pass launch of 1024 threads with few chunks took 1.5 us longer (asum of
-  // 2,024,225, C=16 L=1024, in a graph: 11.1 -> 9.5 us)
-  const bool reads = std::is_integral_v<T> ? wave * kWave < G : wave == 0 || G > kFewLanes * E;
+  const bool few = !std::is_integral_v<T> && G <= kFewLanes * E;
+  const bool reads = std::is_integral_v<T> ? wave * kWave < G : !few;
   if constexpr (COHERENT) {
     if (reads) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
@@ -382,15 +395,18 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
     // this lane's values of the block at b (zeros past the end)
     auto load = [&](int64_t b) {
       const int64_t at = b + (static_cast<int64_t>(wave) * kWave + lane) * E;
-      if (at + E <= G) {
+      if (at + E <= G && !(COHERENT && few)) {
         __builtin_memcpy(v, partials + at, sizeof(v));
         return E;
       }
       int n = 0;
 #pragma unroll
       for (int j = 0; j < E; ++j) {
-        v[j] = at + j < G ? partials[at + j] : A::zero();
-        n += at + j < G ? 1 : 0;
+        v[j] = A::zero();
+        if (at + j < G) {
+          v[j] = COHERENT && few ? load_coherent(partials + at + j) : partials[at + j];
+          ++n;
+        }
       }
       return n;
     };
