@@ -424,10 +424,15 @@ __device__ __forceinline__ void lane_folds(const View& view, bool active, int t,
       // the batch holds operands as loaded; each group is expanded (decoded)
       // just before its fold
       typename View::template Raw<NV> r[U];
+      if constexpr (View::kRawXFirst) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) view.template load_raw_x<NV>(o + u * step, r[u]);
+        for (int u = 0; u < U; ++u) view.template load_raw_x<NV>(o + u * step, r[u]);
 #pragma unroll
-      for (int u = 0; u < U; ++u) view.template load_raw_a<NV>(o + u * step, r[u]);
+        for (int u = 0; u < U; ++u) view.template load_raw_a<NV>(o + u * step, r[u]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) view.template load_raw<NV>(o + u * step, r[u]);
+      }
       __builtin_amdgcn_sched_barrier(0);   // issue the whole batch first
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -474,7 +479,13 @@ __device__ __forceinline__ void lane_folds(const View& view, bool active, int t,
     part = limit - t * C;
     part = (part < 0 ? 0 : (part > C ? C : part)) - nfull * NV;
   }
-  if (__builtin_expect(part > 0, 0)) {
+  if constexpr (ORDER == kContiguous && NV > 4) {
+    for (int v = 0; v < part; ++v) {
+      Term one[1];
+      view.template load<1>(o + v, one);
+      acc[0] = Op::step(one[0], acc[0]);
+    }
+  } else if (__builtin_expect(part > 0, 0)) {
     Term z[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {

@@ -12,6 +12,8 @@ extern template hipError_t launch_gemv<GemvBF16, 8>(const Plan&, const GemvBF16&
                                               hipStream_t);
 extern template hipError_t launch_gemv<GemvFP8, 16>(const Plan&, const GemvFP8&, int64_t, int64_t,
                                               hipStream_t);
+extern template hipError_t launch_gemv<GemvFP8Deep, 16>(const Plan&, const GemvFP8Deep&, int64_t, int64_t,
+                                              hipStream_t);
 extern template hipError_t launch_gemv_thin<GemvF32Deep>(const Plan&, const GemvF32Deep&, int64_t, int64_t,
                                               hipStream_t);
 extern template hipError_t launch_gemv_block<GemvF32, 1>(const Plan&, const GemvF32&, int64_t,
@@ -83,12 +85,15 @@ hipError_t launch_bf16(const Plan& p, const GemvBF16& op, int64_t m, int64_t lda
 }
 
 hipError_t launch_fp8(const Plan& p, const GemvFP8& op, int64_t m, int64_t lda, hipStream_t s) {
-  if (!gemv_blocks<GemvFP8>(p)) return launch_gemv<GemvFP8, 16>(p, op, m, lda, s);
+  const GemvFP8Deep deep{op.A, op.x, op.scale, op.y, op.blas, op.beta_zero, op.alpha, op.beta};
+  if (!gemv_blocks<GemvFP8>(p)) {
+    if (p.C >= 64) return launch_gemv<GemvFP8Deep, 16>(p, deep, m, lda, s);
+    return launch_gemv<GemvFP8, 16>(p, op, m, lda, s);
+  }
   const int64_t waves = block_waves(p, m), cus = device_cus();
   // (lanes shorter than 16 elements have no deep batch)
   if (waves >= 32 * cus || (waves >= 16 * cus && p.C < 16))
     return launch_gemv_block<GemvFP8, 4>(p, op, m, lda, s);
-  const GemvFP8Deep deep{op.A, op.x, op.scale, op.y, op.blas, op.beta_zero, op.alpha, op.beta};
   if (waves >= 16 * cus) return launch_gemv_block<GemvFP8Deep, 4>(p, deep, m, lda, s);
   if (waves >= 6 * cus) return launch_gemv_block<GemvFP8Deep, 2>(p, deep, m, lda, s);
   return launch_gemv_block<GemvFP8Deep, 1>(p, deep, m, lda, s);

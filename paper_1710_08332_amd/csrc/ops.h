@@ -255,6 +255,9 @@ struct GemvF32Acc {
     // flight holds these (1 or 2 bytes per element for the narrow formats)
     // and decodes each group just before it is folded (expand).
     static constexpr bool kRaw = true;
+    // (x's loads first: the headline gemv's batch needs fewer registers; where a
+    // step brings a few codes the folds then wait for the whole batch)
+    static constexpr bool kRawXFirst = kF32;
     template <int NV>
     struct Raw {
       E a[NV];

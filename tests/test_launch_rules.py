@@ -107,3 +107,18 @@ def test_contiguous_lanes_shorter_than_a_row_tile_stay_staged():
              for op in ("dot", "asum") for c, L, n in ((96, 16, 256), (128, 32, 64), (384, 64, 1000))]
     for call, l in first_kernels(rows):
         assert "rows" in l["kernel"], (call, l)
+
+
+CODES = {dp.BF16: "GemvF32Acc<unsigned short, dpia::DecodeBF16, {e}, -1>",
+         dp.FP8_E4M3: "GemvF32Acc<unsigned char, dpia::DecodeFP8, {e}, -1>"}
+
+
+def test_fp8_rows_outside_the_blocks_have_deep_batches_where_lanes_are_long():
+    # (lanes no 16 of which are whole, contiguous rows, teams of more than 256)
+    for C, e in ((63, 0), (64, 64), (171, 64)):
+        calls = [("gemv", dict(seq_len=C, local_size=L, order=o, wg_combine=dp.SEQ),
+                  dict(dtype=dp.FP8_E4M3, m=512, k=L * C, lda=-(-L * C // 16) * 16))
+                 for o, L in ((dp.STRIDED, 8), (dp.STRIDED, 24), (dp.STRIDED, 8192), (dp.STRIDED, 1),
+                              (dp.CONTIGUOUS, 64), (dp.CONTIGUOUS, 300))]
+        for call, l in first_kernels(calls):
+            assert f"gemv_kernel<dpia::{CODES[dp.FP8_E4M3].format(e=e)}" in l["kernel"], (call, l)
