@@ -1,7 +1,9 @@
-"""bf16 and fp8 gemv rows that are not row-blocked: lanes of which no 8 or 16 are
-whole, one or two lanes, teams of more than 256 threads, contiguous lanes of
-every vector width, whole and not.  Rows repeat a few base rows, so that every
-row is compared with the oracle."""
+"""bf16 and fp8 gemv: the row-blocked kernels on both sides of every line of
+their dispatch (tests/test_launch_rules.py holds which kernel that is), with
+remainders of every size of the deep batches; and the rows that are not
+blocked: lanes of which no 8 or 16 are whole, one or two lanes, teams of more
+than 256 threads, contiguous lanes of every vector width, whole and not.  Rows
+repeat a few base rows, so that every row is compared with the oracle."""
 
 import numpy as np
 import pytest
@@ -13,6 +15,7 @@ import paper_1710_08332_amd as dp  # noqa: E402
 import synthetic  # noqa: E402
 from oracle import strategies as S  # noqa: E402
 from tests.gpu_util import assert_same_bits, to_plan  # noqa: E402
+from tests.test_launch_rules import BLOCK_LINES  # noqa: E402
 
 BASE = 37
 
@@ -34,6 +37,18 @@ def check(dt, m, k, s):
         y = dp.gemv(t[:, :k], xt, s, row_scale=torch.from_numpy(scale).cuda()[at])
         want = S.gemv(np.ascontiguousarray(codes[:, :k]), x, to_plan(s), a_format="fp8", scale=scale)
     assert_same_bits(y.cpu().numpy(), want[np.arange(m) % BASE], (dt, m, k, s))
+
+
+@pytest.mark.parametrize("dt,m,C", [c[:3] for c in BLOCK_LINES])
+@pytest.mark.parametrize("short", (0, 5, 512 + 40))
+def test_block_lines(dt, m, C, short):
+    check(dt, m, 512 * C - short, dp.Strategy(seq_len=C, local_size=512, order=dp.STRIDED))
+
+
+@pytest.mark.parametrize("C", (16, 17, 18, 19, 20, 23))
+@pytest.mark.parametrize("m", (3072, 8192))
+def test_remainders_of_the_deep_batch(m, C):
+    check(dp.FP8_E4M3, m, 512 * C, dp.Strategy(seq_len=C, local_size=512, order=dp.STRIDED))
 
 
 @pytest.mark.parametrize("dt", (dp.BF16, dp.FP8_E4M3))
