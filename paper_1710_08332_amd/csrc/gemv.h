@@ -433,6 +433,10 @@ hipError_t launch_gemv_block(const Plan& p, const Op& op, int64_t m, int64_t lda
   // least 64 threads)
   a.teams_per_wg = p.team < kWave ? kWave / p.team : 1;
   if (a.teams_per_wg > p.teams_per_wg) a.teams_per_wg = p.teams_per_wg;
+  if (grid_is_bound(p, (m + a.teams_per_wg * RB - 1) / (a.teams_per_wg * RB))) {
+    a.teams_per_wg = 256 / p.team;
+    if (a.teams_per_wg > p.teams_per_wg) a.teams_per_wg = p.teams_per_wg;
+  }
   a.team_lds_elems = (p.combine == DPIA_COMBINE_SEQ) ? static_cast<int>(p.L)
                                                      : (p.team > 64 ? p.team / 64 : 1);
   a.parts = p.row_parts;
@@ -539,7 +543,7 @@ hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda,
     a.L = static_cast<int>(p.L);
     a.C = static_cast<int>(p.C);
     a.parts = p.row_parts;
-    a.teams_per_wg = rows_teams(slices, m, device_cus());
+    a.teams_per_wg = rows_teams(slices, m, bounded_grid(device_cus(), p.max_grid, kWave));
     const int waves =
         slices >= kRowsWaves ? kRowsWaves : a.teams_per_wg * static_cast<int>(slices);
     a.stage_off = kRowsScratch +
@@ -567,12 +571,6 @@ hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda,
 // lanes are in flight whole with four of them to a thread (us, that and one to
 // a thread: 1024 rows of L=64, C=8 2.5 3.4, C=16 3.4 3.8, C=24 4.3 4.5, C=32
 // 4.8 4.4, C=64 7.9 6.3; 64 rows of L=32, C=32 3.4 3.6, C=48 4.8 4.3).
-inline bool gemv_thin(const Plan& p, int64_t m) {
-  const int64_t lanes = m * p.L, cus = device_cus();
-  return p.order == DPIA_ORDER_STRIDED && p.nv == 4 && p.team >= 4 && p.L <= 256 &&
-         lanes <= 256 * cus && p.C >= (lanes < 16 * cus ? 48 : 32);
-}
-
 inline Plan gemv_thin_plan(const Plan& p, int64_t m) {
   Plan q = p;
   q.nv = 1;
@@ -586,6 +584,17 @@ inline Plan gemv_thin_plan(const Plan& p, int64_t m) {
   q.lds_bytes = (static_cast<size_t>(q.teams_per_wg) * per_team * sizeof(float) + 31) / 16 * 16;
   q.stage = false;
   return q;
+}
+
+// (A bounded grid has to be large enough for work-groups of fewer than 256
+// threads: 4096 x 1024, C=64 L=16 under 300 work-groups 12.3 us, 8.5 not thin.)
+inline bool gemv_thin(const Plan& p, int64_t m) {
+  const int64_t lanes = m * p.L, cus = device_cus();
+  if (p.order != DPIA_ORDER_STRIDED || p.nv != 4 || p.team < 4 || p.L > 256 ||
+      lanes > 256 * cus || p.C < (lanes < 16 * cus ? 48 : 32))
+    return false;
+  const Plan q = gemv_thin_plan(p, m);
+  return q.wg_threads >= 256 || !grid_is_bound(q, (m + q.teams_per_wg - 1) / q.teams_per_wg);
 }
 
 // Whether staged contiguous teams are launched one wavefront's worth (or one
@@ -642,7 +651,8 @@ hipError_t launch_gemv(const Plan& p, const Op& op, int64_t m, int64_t lda, hipS
   GemvArgs a = gemv_args(p, m, lda);
   Plan q = p;
   const int teams = p.team < kWave ? kWave / p.team : 1;
-  if (teams < p.teams_per_wg && p.nv == MAXNV && gemv_by_wave(p, Op::kF32Rows)) {
+  if (teams < p.teams_per_wg && p.nv == MAXNV && gemv_by_wave(p, Op::kF32Rows) &&
+      (p.max_grid == 0 || (m + teams - 1) / teams <= static_cast<int64_t>(p.max_grid))) {
     q.teams_per_wg = a.teams_per_wg = teams;
     q.wg_threads = teams * p.team;
     const size_t lanes = static_cast<size_t>(teams) * a.team_lds_elems * sizeof(typename Op::T);

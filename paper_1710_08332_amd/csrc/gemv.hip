@@ -55,7 +55,8 @@ namespace {
 // 16384^2 C=512 L=32 160.5, 166.6, 3432 x 15745 C=124 L=128 37.4, 38.5).
 bool gemv_halves(const Plan& p, int64_t m) {
   return gemv_blocks<GemvF32>(p) && (p.L == 64 || p.L == 128) && p.C >= 64 &&
-         m * p.team >= 8 * kWave * static_cast<int64_t>(device_cus());
+         m * p.team >= 8 * kWave * static_cast<int64_t>(device_cus()) &&
+         !grid_is_bound(p, m * p.team / kWave);
 }
 
 // Row-blocked bf16 / fp8 rows.  More rows per team share each load of x;
@@ -73,12 +74,15 @@ bool gemv_halves(const Plan& p, int64_t m) {
 //        16384 x 8192 C=128 L=64 (1024)  4x16 113   4x64 59.6  2x64 44.3  1x64 41.1
 // (with 256-thread work-groups, 2 rows and 16 elements, the four bf16 rows
 // took 95.4, 53.2, 29.3 and 32.0 us, the fifth 192.)
+// (a bounded grid: 2 bf16 rows instead of 4, 2 fp8 rows instead of 1, as the
+// work-groups of launch_gemv_block are large then)
 int64_t block_waves(const Plan& p, int64_t m) { return (m * p.team + kWave - 1) / kWave; }
 
 hipError_t launch_bf16(const Plan& p, const GemvBF16& op, int64_t m, int64_t lda, hipStream_t s) {
   if (!gemv_blocks<GemvBF16>(p)) return launch_gemv<GemvBF16, 8>(p, op, m, lda, s);
   const int64_t waves = block_waves(p, m), cus = device_cus();
-  if (waves >= 64 * cus) return launch_gemv_block<GemvBF16, 4>(p, op, m, lda, s);
+  if (waves >= 64 * cus && !grid_is_bound(p, waves / 4))
+    return launch_gemv_block<GemvBF16, 4>(p, op, m, lda, s);
   if (waves >= 16 * cus) return launch_gemv_block<GemvBF16, 2>(p, op, m, lda, s);
   const GemvBF16Deep deep{op.A, op.x, op.scale, op.y, op.blas, op.beta_zero, op.alpha, op.beta};
   return launch_gemv_block<GemvBF16Deep, 1>(p, deep, m, lda, s);
@@ -95,7 +99,8 @@ hipError_t launch_fp8(const Plan& p, const GemvFP8& op, int64_t m, int64_t lda, 
   if (waves >= 32 * cus || (waves >= 16 * cus && p.C < 16))
     return launch_gemv_block<GemvFP8, 4>(p, op, m, lda, s);
   if (waves >= 16 * cus) return launch_gemv_block<GemvFP8Deep, 4>(p, deep, m, lda, s);
-  if (waves >= 6 * cus) return launch_gemv_block<GemvFP8Deep, 2>(p, deep, m, lda, s);
+  if (waves >= 6 * cus || grid_is_bound(p, waves))
+    return launch_gemv_block<GemvFP8Deep, 2>(p, deep, m, lda, s);
   return launch_gemv_block<GemvFP8Deep, 1>(p, deep, m, lda, s);
 }
 

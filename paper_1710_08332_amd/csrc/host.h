@@ -36,6 +36,18 @@ inline int64_t bounded_grid(int64_t need, uint32_t max_grid, int64_t threads) {
   return need < most ? need : most;
 }
 
+// Whether the strategy's max_grid leaves fewer work-groups than `need`, and
+// fewer than 4 per compute unit.  What is in flight is then the work-group's
+// share, so launches that would take small ones, or little per thread, take
+// the largest their plan has.  (With 4 one-wavefront work-groups per compute
+// unit they are as fast as without a bound or faster than large ones: bf16
+// 16384^2 C=32 L=512, bounds of 1024 / 256 / 64: 84 / 215 / 831 us in work-groups
+// of one wavefront, 98 / 105 / 368 in those of four.)
+inline bool grid_is_bound(const Plan& p, int64_t need) {
+  return p.max_grid && need > static_cast<int64_t>(p.max_grid) &&
+         static_cast<int64_t>(p.max_grid) < 4 * static_cast<int64_t>(device_cus());
+}
+
 // Work-groups to launch: one per group of `teams_per_wg` items, capped at
 // what the device keeps resident (or at the strategy's max_grid).  The
 // kernels distribute items by a grid-stride loop, so this never changes a

@@ -37,6 +37,39 @@ __global__ void __launch_bounds__(kMapThreads) scal_kernel(float alpha, const fl
   }
 }
 
+// The same where the strategy bounds the grid and a work-group makes many
+// pieces: 8 of each thread in flight (2^26 elements, bounds of 64 / 256 / 512:
+// one piece 541, 168, 102 us, 8 pieces 184, 87, 89).
+__global__ void __launch_bounds__(kMapThreads) scal_bound_kernel(float alpha, const float* x,
+                                                                 float* y, int64_t n) {
+  constexpr int U = 8;
+  constexpr int64_t kPer = kMapThreads * 4 * U;
+  for (int64_t base = static_cast<int64_t>(blockIdx.x) * kPer; base < n;
+       base += static_cast<int64_t>(gridDim.x) * kPer) {
+    const int64_t first = base + static_cast<int64_t>(threadIdx.x) * 4;
+    if (base + kPer <= n) {
+      f32x4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        v[u] = __builtin_nontemporal_load(
+            reinterpret_cast<const f32x4*>(x + first + u * (kMapThreads * 4)));
+      __builtin_amdgcn_sched_barrier(0);   // issue all loads first
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[u][j] = alpha * v[u][j];
+        __builtin_nontemporal_store(
+            v[u], reinterpret_cast<f32x4*>(y + first + u * (kMapThreads * 4)));
+      }
+    } else {
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = first + u * (kMapThreads * 4);
+        for (int64_t j = i; j < i + 4 && j < n; ++j) y[j] = alpha * x[j];
+      }
+    }
+  }
+}
+
 }  // namespace dpia
 
 using namespace dpia;
@@ -56,11 +89,13 @@ extern "C" dpia_status dpia_scal(const dpia_strategy* s, dpia_dtype dt, int64_t 
   }
   // one work-group per 1,024 elements, or the strategy's bound on them
   constexpr int64_t kPer = kMapThreads * 4;
-  const int64_t grid = bounded_grid((p.n + kPer - 1) / kPer, p.max_grid, kMapThreads);
+  const int64_t need = (p.n + kPer - 1) / kPer;
+  auto kern = grid_is_bound(p, need) ? scal_bound_kernel : scal_kernel;
+  const int64_t grid = bounded_grid(need, p.max_grid, kMapThreads);
   const float* xp = static_cast<const float*>(x);
   float* yp = static_cast<float*>(y);
   void* args[] = {&alpha, &xp, &yp, &p.n};
-  hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(scal_kernel), dim3(grid),
+  hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(grid),
                                  dim3(kMapThreads), args, 0, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "dpia_scal launch");
   clear_detail();

@@ -477,7 +477,8 @@ inline Plan thin_plan(const Plan& p) {
   q.teams_per_wg = q.team >= kThinTeam ? 1 : kThinTeam / q.team;
   while ((q.passes == 2 || q.C >= kThinRound) && q.teams_per_wg > 1 &&
          (q.teams_per_wg / 2) * q.team >= kWave &&
-         (q.items + q.teams_per_wg - 1) / q.teams_per_wg < device_cus())
+         (q.items + q.teams_per_wg - 1) / q.teams_per_wg <
+             bounded_grid(device_cus(), q.max_grid, kThinTeam))
     q.teams_per_wg /= 2;
   q.wg_threads = q.teams_per_wg * q.team;
   size_t lds = 0;
@@ -545,7 +546,9 @@ hipError_t launch_rows(const Plan& p, const Op& op, const ReduceArgs& a, int row
     constexpr int D = ROWS == kWave ? 1 : (NOPS == 1 ? 4 : 2);
     const int64_t slices = p.L / ROWS;
     ReduceArgs a_copy = a;
-    a_copy.teams_per_wg = rows_teams(slices, p.items, a.one_pass ? device_cus() / 4 : device_cus());
+    a_copy.teams_per_wg =
+        rows_teams(slices, p.items,
+                   bounded_grid(a.one_pass ? device_cus() / 4 : device_cus(), p.max_grid, kWave));
     const int waves = slices >= kRowsWaves
                           ? kRowsWaves : a_copy.teams_per_wg * static_cast<int>(slices);
     a_copy.stage_off = kRowsScratch;

@@ -140,3 +140,31 @@ def test_fp8_rows_outside_the_blocks_have_deep_batches_where_lanes_are_long():
                               (dp.CONTIGUOUS, 64), (dp.CONTIGUOUS, 300))]
         for call, l in first_kernels(calls):
             assert f"gemv_kernel<dpia::{CODES[dp.FP8_E4M3].format(e=e)}" in l["kernel"], (call, l)
+
+
+def test_work_groups_of_a_bounded_grid_are_large():
+    # a wavefront, or a 16-byte piece a thread, to a work-group leaves a bound
+    # of a few hundred work-groups with little in flight
+    def calls(g):
+        return [("gemv", dict(seq_len=64, local_size=64, max_grid=g), dict(m=16384, k=4096)),
+                ("gemv", dict(seq_len=256, local_size=32, max_grid=g), dict(m=8192, k=8192)),
+                ("gemv", dict(seq_len=64, local_size=128, max_grid=g), dict(dtype=dp.BF16, m=8192, k=8192)),
+                ("gemv", dict(seq_len=64, local_size=64, max_grid=g), dict(dtype=dp.FP8_E4M3, m=16384, k=4096)),
+                ("gemv", dict(seq_len=32, local_size=512, order=dp.STRIDED, max_grid=g),
+                 dict(dtype=dp.BF16, m=16384, k=16384)),
+                ("gemv", dict(seq_len=64, local_size=256, order=dp.STRIDED, max_grid=g),
+                 dict(dtype=dp.FP8_E4M3, m=16384, k=16384)),
+                ("gemv", dict(seq_len=64, local_size=128, order=dp.STRIDED, max_grid=g), dict(m=8192, k=8192)),
+                ("gemv", dict(seq_len=64, local_size=16, order=dp.STRIDED, max_grid=g), dict(m=4096, k=1024)),
+                ("gemv", dict(seq_len=1024, local_size=16, max_grid=g), dict(m=256, k=16384)),
+                ("dot", dict(seq_len=256, local_size=16, max_grid=g), dict(n=1 << 20)),
+                ("scal", dict(seq_len=64, local_size=256, max_grid=g), dict(n=1 << 24))]
+    for call, l in first_kernels(calls(60)):
+        assert l["block"] == 256 and l["grid"] <= 60, (call, l)
+    assert "scal_bound_kernel" in first_kernels(calls(60))[-1][1]["kernel"]
+    assert [l["block"] for _, l in first_kernels(calls(0))][:8] == [64] * 8
+    # few fp8 rows: one to a team, two under a bound
+    few = [("gemv", dict(seq_len=64, local_size=64, order=dp.STRIDED, max_grid=g),
+            dict(dtype=dp.FP8_E4M3, m=4096, k=4096)) for g in (0, 60)]
+    for (call, l), rows in zip(first_kernels(few), (1, 2)):
+        assert f", 16, 0, {rows}>" in l["kernel"], (call, l)
