@@ -155,7 +155,6 @@ def test_work_groups_of_a_bounded_grid_are_large():
                 ("gemv", dict(seq_len=64, local_size=256, order=dp.STRIDED, max_grid=g),
                  dict(dtype=dp.FP8_E4M3, m=16384, k=16384)),
                 ("gemv", dict(seq_len=64, local_size=128, order=dp.STRIDED, max_grid=g), dict(m=8192, k=8192)),
-                ("gemv", dict(seq_len=64, local_size=16, order=dp.STRIDED, max_grid=g), dict(m=4096, k=1024)),
                 ("gemv", dict(seq_len=1024, local_size=16, max_grid=g), dict(m=256, k=16384)),
                 ("dot", dict(seq_len=256, local_size=16, max_grid=g), dict(n=1 << 20)),
                 ("scal", dict(seq_len=64, local_size=256, max_grid=g), dict(n=1 << 24))]
@@ -163,6 +162,11 @@ def test_work_groups_of_a_bounded_grid_are_large():
         assert l["block"] == 256 and l["grid"] <= 60, (call, l)
     assert "scal_bound_kernel" in first_kernels(calls(60))[-1][1]["kernel"]
     assert [l["block"] for _, l in first_kernels(calls(0))][:8] == [64] * 8
+    # few strided lanes: four to a thread under a bound
+    few = [("gemv", dict(seq_len=64, local_size=16, order=dp.STRIDED, max_grid=g), dict(m=4096, k=1024))
+           for g in (0, 60)]
+    for (call, l), lanes in zip(first_kernels(few), (1, 4)):
+        assert f"-1>, 1, {lanes}, 0, 256, false>" in l["kernel"], (call, l)
     # few fp8 rows: one to a team, two under a bound
     few = [("gemv", dict(seq_len=64, local_size=64, order=dp.STRIDED, max_grid=g),
             dict(dtype=dp.FP8_E4M3, m=4096, k=4096)) for g in (0, 60)]
