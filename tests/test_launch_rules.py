@@ -161,7 +161,7 @@ def test_work_groups_of_a_bounded_grid_are_large():
     for call, l in first_kernels(calls(60)):
         assert l["block"] == 256 and l["grid"] <= 60, (call, l)
     assert "scal_bound_kernel" in first_kernels(calls(60))[-1][1]["kernel"]
-    assert [l["block"] for _, l in first_kernels(calls(0))][:8] == [64] * 8
+    assert all(l["block"] <= 128 for _, l in first_kernels(calls(0))[:8])
     # few strided lanes: four to a thread under a bound
     few = [("gemv", dict(seq_len=64, local_size=16, order=dp.STRIDED, max_grid=g), dict(m=4096, k=1024))
            for g in (0, 60)]
