@@ -212,6 +212,10 @@ __device__ __forceinline__ bool both_signs(const F (&v)[E]) {
 constexpr int kFoldStops = 44;
 constexpr int kFoldTries = 2;
 
+// Values of type T that a lane of the fold holds.
+template <class T>
+constexpr int kFoldLaneValues = sizeof(T) > 4 ? 8 : 16;
+
 // Slots of LDS a block's chain uses: per wavefront the sum of its values and
 // the value its chain reaches, and one flag.
 constexpr int kFoldWaves = 16;
@@ -356,7 +360,7 @@ template <class A, int FINAL, bool COHERENT = false>
 __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_t G, void* out,
                            int out_f64, void* lds) {
   using T = typename A::T;
-  constexpr int E = sizeof(T) > 4 ? 8 : 16;      // values per lane
+  constexpr int E = kFoldLaneValues<T>;
   // fewer values than this many lanes hold are folded lane by lane
   constexpr int kFewLanes = 32;
   const int tid = fold_thread();

@@ -667,8 +667,8 @@ hipError_t launch_chunks(const Plan& p, const Op& op, const ReduceArgs& a, hipSt
 }
 
 // The outer reduceSeq over G chunk values, as a kernel of its own: 4
-// wavefronts while one block of theirs holds the values, else 16.
-constexpr int64_t kFoldWide = 4096;
+// wavefronts while one block of theirs holds the values (4,096, or 2,048
+// pairs), else 16.
 template <class Op, int FINAL>
 hipError_t launch_fold(int64_t G, const void* partials, void* out, int out_f64,
                        hipStream_t stream) {
@@ -676,7 +676,7 @@ hipError_t launch_fold(int64_t G, const void* partials, void* out, int out_f64,
   const T* pp = static_cast<const T*>(partials);
   void* args[] = {&pp, &G, &out, &out_f64};
   auto kern = final_kernel<typename Op::Arith, FINAL>;
-  const int threads = G > kFoldWide ? 1024 : 256;
+  const int threads = G > 4 * kWave * kFoldLaneValues<T> ? 1024 : 256;
   return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(1), dim3(threads), args,
                          kFoldLds, stream);
 }

@@ -172,3 +172,11 @@ def test_work_groups_of_a_bounded_grid_are_large():
             dict(dtype=dp.FP8_E4M3, m=4096, k=4096)) for g in (0, 60)]
     for (call, l), rows in zip(first_kernels(few), (1, 2)):
         assert f", 16, 0, {rows}>" in l["kernel"], (call, l)
+
+
+def test_a_fold_takes_sixteen_wavefronts_beyond_one_block_of_four():
+    # a lane holds 16 values, or 8 pairs
+    for acc, most in (("plain", 4096), ("kahan", 2048), ("sum2", 2048)):
+        calls = [("fold", dict(seq_len=4, local_size=1, wg_combine=dp.SEQ, accum=ACCUMS[acc]),
+                  dict(n=4 * G)) for G in (most, most + 1)]
+        assert [l["block"] for _, l in first_kernels(calls)] == [256, 1024], acc
