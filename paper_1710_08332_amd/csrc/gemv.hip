@@ -63,17 +63,24 @@ bool gemv_halves(const Plan& p, int64_t m) {
 // fewer, with deeper batches, keep the memory busy when there are few
 // wavefronts.  `waves`: wavefronts of the launch with one row per team.
 // Measured with 64-thread work-groups (us; rows per team x elements per batch):
-//  bf16  16384^2 C=32 L=512 (16384 waves)    4x16 83.5  2x16 85.1  1x64 107.6
-//        16384 x 8192 C=32 L=256 (8192)      4x16 44.3  2x16 43.3  1x64 47.1
-//        4096 x 16384 C=32 L=512 (4096)      4x16 25.3  2x16 23.3  1x64 29.0
-//        4096 x 16384 C=64 L=256 (2048)      4x16 34.1  2x16 28.4  1x64 25.4
-//        1024 x 16384 C=512 L=32 (64)        4x16 211   2x16 177   1x64 62
-//  fp8   16384^2 C=32 L=512 (8192)    4x16 45.5  4x64 49.4  2x64 53.4  1x64 72.6
-//        16384^2 C=64 L=256 (4096)    4x16 63.8  4x64 49.2  2x64 49.0  1x64 72.8
-//        4096 x 16384 C=32 L=512 (2048)  4x16 29.7  4x64 19.3  2x64 15.5  1x64 23.1
-//        16384 x 8192 C=128 L=64 (1024)  4x16 113   4x64 59.6  2x64 44.3  1x64 41.1
-// (with 256-thread work-groups, 2 rows and 16 elements, the four bf16 rows
-// took 95.4, 53.2, 29.3 and 32.0 us, the fifth 192.)
+//  bf16  L=256 C=16   2048 waves   1x64 11.7  2x16 11.9     3000  19.8  13.5
+//              C=64   2048         27.1  31.0               3000  43.0  35.6
+//        L=512 C=32   1024         11.7  15.4  2048  18.9  17.6  3000  32.2  21.0
+//              C=32   8000         66.5  50.5  4x16 49.4   16384  131  96.5  96.5
+//  fp8   L=512 C=32   1400 waves   1x64 20.6  2x64 17.2  4x64 24.0  4x16 33.6
+//                     2000         26.3  18.8  25.7  35.3
+//                     3000         45.5  34.5  28.2  37.1
+//                     4600         --    37.5  39.9  34.8
+//                     9000         --    63.0  61.8  69.7
+//              C=16   4600         --    23.2  23.5  20.2
+//        L=256 C=64   4000         81.1  61.3  55.9  72.6   8000  --  120  108  125
+//        L=64  C=16   12000        --    50.7  47.9  59.6
+// Hence: bf16 1x64 up to 8 wavefronts per compute unit (6 with 64 threads to a
+// team), 2x16 up to 64, 4x16; fp8 1x64 up to 6, 2x64 up to 8, 4x64 up to 16,
+// then 4x16, but 4x64 for narrow teams and for long lanes where it wins.  (With
+// 256-thread work-groups, 2 rows and 16 elements, the bf16 launches of 2048 and
+// 3000 wavefronts above took 12.3, 13.7, 32.2, 39.2, 18.7 and 21.2 us; the fp8
+// ones, of 2 or 4 rows, 34.6, 36.0, 40.0, 37.9, 65.5, 20.2, 82.7, 155 and 51.3.)
 // (a bounded grid: 2 bf16 rows instead of 4, 2 fp8 rows instead of 1, as the
 // work-groups of launch_gemv_block are large then)
 int64_t block_waves(const Plan& p, int64_t m) { return (m * p.team + kWave - 1) / kWave; }
@@ -83,7 +90,8 @@ hipError_t launch_bf16(const Plan& p, const GemvBF16& op, int64_t m, int64_t lda
   const int64_t waves = block_waves(p, m), cus = device_cus();
   if (waves >= 64 * cus && !grid_is_bound(p, waves / 4))
     return launch_gemv_block<GemvBF16, 4>(p, op, m, lda, s);
-  if (waves >= 16 * cus) return launch_gemv_block<GemvBF16, 2>(p, op, m, lda, s);
+  if (waves > (p.team >= kWave ? 6 : 8) * cus)
+    return launch_gemv_block<GemvBF16, 2>(p, op, m, lda, s);
   const GemvBF16Deep deep{op.A, op.x, op.scale, op.y, op.blas, op.beta_zero, op.alpha, op.beta};
   return launch_gemv_block<GemvBF16Deep, 1>(p, deep, m, lda, s);
 }
@@ -95,11 +103,13 @@ hipError_t launch_fp8(const Plan& p, const GemvFP8& op, int64_t m, int64_t lda, 
     return launch_gemv<GemvFP8, 16>(p, op, m, lda, s);
   }
   const int64_t waves = block_waves(p, m), cus = device_cus();
-  // (lanes shorter than 16 elements have no deep batch)
-  if (waves >= 32 * cus || (waves >= 16 * cus && p.C < 16))
+  if (waves > 8 * cus) {
+    const bool deep4 = waves <= 16 * cus || p.team <= 4 || (p.C >= 64 && p.team <= 16) ||
+                       (waves > 32 * cus && p.C >= 32 && (p.team <= 16 || waves < 56 * cus));
+    if (deep4) return launch_gemv_block<GemvFP8Deep, 4>(p, deep, m, lda, s);
     return launch_gemv_block<GemvFP8, 4>(p, op, m, lda, s);
-  if (waves >= 16 * cus) return launch_gemv_block<GemvFP8Deep, 4>(p, deep, m, lda, s);
-  if (waves >= 6 * cus || grid_is_bound(p, waves))
+  }
+  if (waves > 6 * cus || grid_is_bound(p, waves))
     return launch_gemv_block<GemvFP8Deep, 2>(p, deep, m, lda, s);
   return launch_gemv_block<GemvFP8Deep, 1>(p, deep, m, lda, s);
 }

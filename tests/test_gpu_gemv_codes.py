@@ -39,14 +39,14 @@ def check(dt, m, k, s):
     assert_same_bits(y.cpu().numpy(), want[np.arange(m) % BASE], (dt, m, k, s))
 
 
-@pytest.mark.parametrize("dt,m,C", [c[:3] for c in BLOCK_LINES])
-@pytest.mark.parametrize("short", (0, 5, 512 + 40))
-def test_block_lines(dt, m, C, short):
-    check(dt, m, 512 * C - short, dp.Strategy(seq_len=C, local_size=512, order=dp.STRIDED))
+@pytest.mark.parametrize("dt,m,C,L", [c[:4] for c in BLOCK_LINES])
+@pytest.mark.parametrize("steps,short", ((0, 0), (0, 5), (1, 40)))
+def test_block_lines(dt, m, C, L, steps, short):
+    check(dt, m, L * (C - steps) - short, dp.Strategy(seq_len=C, local_size=L, order=dp.STRIDED))
 
 
 @pytest.mark.parametrize("C", (16, 17, 18, 19, 20, 23))
-@pytest.mark.parametrize("m", (3072, 8192))
+@pytest.mark.parametrize("m", (4096, 8192))
 def test_remainders_of_the_deep_batch(m, C):
     check(dp.FP8_E4M3, m, 512 * C, dp.Strategy(seq_len=C, local_size=512, order=dp.STRIDED))
 

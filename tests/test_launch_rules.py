@@ -112,20 +112,26 @@ def test_contiguous_lanes_shorter_than_a_row_tile_stay_staged():
 CODES = {dp.BF16: "GemvF32Acc<unsigned short, dpia::DecodeBF16, {e}, -1>",
          dp.FP8_E4M3: "GemvF32Acc<unsigned char, dpia::DecodeFP8, {e}, -1>"}
 
-# (matrix type, rows, elements of a lane) over 512 strided lanes, where the
-# launch changes: rows per team, elements per batch (0: 16)
+# (matrix type, rows, elements of a lane, lanes) where the launch changes: rows
+# per team, elements per batch (0: 16)
 BLOCK_LINES = [
-    (dp.BF16, 4095, 17, 1, 64), (dp.BF16, 4096, 17, 2, 0), (dp.BF16, 16383, 17, 2, 0),
-    (dp.BF16, 16384, 17, 4, 0), (dp.FP8_E4M3, 3070, 17, 1, 64), (dp.FP8_E4M3, 3072, 17, 2, 64),
-    (dp.FP8_E4M3, 8190, 17, 2, 64), (dp.FP8_E4M3, 8192, 15, 4, 0), (dp.FP8_E4M3, 8192, 16, 4, 64),
-    (dp.FP8_E4M3, 16382, 19, 4, 64), (dp.FP8_E4M3, 16384, 19, 4, 0),
+    (dp.BF16, 1536, 17, 512, 1, 64), (dp.BF16, 1537, 17, 512, 2, 0), (dp.BF16, 4096, 17, 256, 1, 64),
+    (dp.BF16, 4097, 17, 256, 2, 0), (dp.BF16, 16383, 17, 512, 2, 0), (dp.BF16, 16384, 17, 512, 4, 0),
+    (dp.FP8_E4M3, 3072, 17, 512, 1, 64), (dp.FP8_E4M3, 3074, 17, 512, 2, 64),
+    (dp.FP8_E4M3, 4096, 17, 512, 2, 64), (dp.FP8_E4M3, 4098, 17, 512, 4, 64),
+    (dp.FP8_E4M3, 8192, 15, 512, 4, 64), (dp.FP8_E4M3, 8194, 19, 512, 4, 0),
+    (dp.FP8_E4M3, 65552, 17, 64, 4, 64), (dp.FP8_E4M3, 32776, 17, 128, 4, 0),
+    (dp.FP8_E4M3, 16388, 63, 256, 4, 0), (dp.FP8_E4M3, 16388, 64, 256, 4, 64),
+    (dp.FP8_E4M3, 32768, 32, 256, 4, 0), (dp.FP8_E4M3, 32772, 32, 256, 4, 64),
+    (dp.FP8_E4M3, 32772, 31, 256, 4, 0), (dp.FP8_E4M3, 28670, 33, 512, 4, 64),
+    (dp.FP8_E4M3, 28672, 33, 512, 4, 0),
 ]
 
 
 def test_row_blocks_of_codes():
-    calls = [("gemv", dict(seq_len=C, local_size=512, order=dp.STRIDED), dict(dtype=dt, m=m, k=512 * C))
-             for dt, m, C, _, _ in BLOCK_LINES]
-    for (call, l), (dt, m, C, rows, e) in zip(first_kernels(calls), BLOCK_LINES):
+    calls = [("gemv", dict(seq_len=C, local_size=L, order=dp.STRIDED), dict(dtype=dt, m=m, k=L * C))
+             for dt, m, C, L, _, _ in BLOCK_LINES]
+    for (call, l), (dt, m, C, L, rows, e) in zip(first_kernels(calls), BLOCK_LINES):
         nv = 8 if dt == dp.BF16 else 16
         want = f"gemv_block_kernel<dpia::{CODES[dt].format(e=e)}, {nv}, 0, {rows}>"
         assert want in l["kernel"], (call, l)
