@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(kWave*(1 + kFedLoaders)) fed_reduce_kernel(Op 
       if (limit == a.W)
         fed_fold_strided<Op, ROWS>(view, a.L, a.C, wave, lane, row0, ring, acc[0]);
       else if (wave == 0)
-        lane_folds<Op, kStrided, 1>(view, lane < ROWS, row0 + lane, a.L, a.C, limit, acc);
+        lane_folds<OneLane<Op>, kStrided, 1>(view, lane < ROWS, row0 + lane, a.L, a.C, limit, acc);
     } else {
       if (limit == a.W)
         fed_fold<Op, VEC, ROWS>(view, Cel, wave, lane, row0, ring, acc);

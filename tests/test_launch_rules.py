@@ -186,3 +186,11 @@ def test_a_fold_takes_sixteen_wavefronts_beyond_one_block_of_four():
         calls = [("fold", dict(seq_len=4, local_size=1, wg_combine=dp.SEQ, accum=ACCUMS[acc]),
                   dict(n=4 * G)) for G in (most, most + 1)]
         assert [l["block"] for _, l in first_kernels(calls)] == [256, 1024], acc
+
+
+def test_chunks_of_long_strided_lanes_are_fed_whole_or_not():
+    calls = [(op, dict(seq_len=1024, local_size=L, order=dp.STRIDED, wg_combine=dp.TREE),
+              dict(n=3 * 1024 * L + r)) for op in ("dot", "asum") for L in (16, 64, 256)
+             for r in (0, 1, 1024 * L - 1)]
+    for call, l in first_kernels(calls):
+        assert "fed_reduce_kernel" in l["kernel"], (call, l)
