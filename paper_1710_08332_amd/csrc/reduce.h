@@ -452,15 +452,26 @@ inline int thin_nv(const Plan& p) {
 // part from 16: 8 chunks of C=16 L=64 4.8 us not thin, 4.0 thin; whole 3.6,
 // 3.7), and its work-groups hold 256 threads up to 64 (256 chunks of L=64, dot:
 // C=16 5.7 us not thin, 7.9 in work-groups of one wavefront, 5.8 in full ones;
-// C=32 7.2, 8.4, 6.7; C=64 8.9, 8.6, 7.4); where those are more than 256 then,
-// 512 chunks of C=32 L=256, an asum takes 10.9 us not thin, 11.4 thin.
+// C=32 7.2, 8.4, 6.7; C=64 8.9, 8.6, 7.4).  Teams of a few threads put so many
+// chunks into a work-group that there are too few of those: such lanes are one
+// to a thread whatever their length, from where it pays (1 pass, asum C=8, not
+// thin and thin; lanes in the launch):
+//   L=4   8,192 6.9 6.2    16,384 9.9 6.8   65,536 28.8 15.8
+//   L=16  24,576 7.5 6.8   32,768 7.6 6.9   65,536 11.8 8.8
+//   L=32  32,768 5.9 6.6   49,152 8.9 8.0   65,536 9.1 8.5
+// Wider ones beyond 384 lanes per compute unit have work-groups enough, each
+// thin one more to arrive (asum C=32 L=64, 65,536 lanes 9.7 9.0; 98,304 12.6
+// 10.5; 131,072 10.8 11.1; 262,144 13.3 16.0; L=256, 98,304 10.1 9.3; 131,072
+// 10.5 10.8).
 constexpr int kThinRound = 64;     // elements a lane has in flight at once
 inline bool thin_lanes(const Plan& p) {
   if (p.order != DPIA_ORDER_STRIDED || p.V != 1 || p.nv == 1 || !thin_nv(p)) return false;
   const int64_t lanes = p.items * p.L, cus = device_cus();
   if (p.passes == 1) {
     const bool part = p.op == DPIA_OP_DOT && p.n % p.W != 0;
-    if (p.C < (part ? 16 : 32) || (p.C < kThinRound && lanes > 256 * cus)) return false;
+    const int64_t narrow = p.L <= 8 ? 64 : p.L <= 16 ? 128 : p.L <= 32 ? 192 : INT64_MAX / cus;
+    if (p.C < (part ? 16 : 32) && lanes < narrow * cus) return false;
+    if (p.C < kThinRound && p.L >= kWave && lanes > 384 * cus) return false;
   } else if (p.L >= kWave && p.C < (p.op == DPIA_OP_ASUM ? 16 : 8)) {
     return false;
   }

@@ -81,6 +81,19 @@ def test_short_strided_lanes_keep_four_to_a_thread():
     for call, l in first_kernels(long):
         assert "float, dpia::DecodeF32, 64" in l["kernel"], (call, l)
 
+    # narrow teams: so many chunks to a work-group, so few work-groups
+    for L, least in ((4, 64), (8, 64), (16, 128), (32, 192)):
+        for lanes, deep in ((least * 256 - L, False), (least * 256, True), (60000 // L * L, True)):
+            calls = [(op, dict(seq_len=C, local_size=L, passes=1, **G), dict(n=C * lanes))
+                     for op in ("dot", "asum") for C in (2, 8, 24)]
+            for call, l in first_kernels(calls):
+                assert ("Deep<" in l["kernel"]) == deep, (call, l)
+    # wide ones: work-groups enough
+    for lanes, deep in ((384 * 256, True), (384 * 256 + 64, False), (1 << 18, False)):
+        calls = [("asum", dict(seq_len=C, local_size=64, passes=1, **G), dict(n=C * lanes)) for C in (32, 63)]
+        for call, l in first_kernels(calls):
+            assert ("Deep<" in l["kernel"]) == deep, (call, l)
+
 
 def test_one_pass_launches_of_short_lanes_hold_256_threads():
     # 256 chunks of 64 lanes: 64 work-groups to arrive, not 256
