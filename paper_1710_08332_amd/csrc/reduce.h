@@ -524,13 +524,14 @@ inline Plan thin_plan(const Plan& p) {
 //   asum 256 chunks of L=32  C=32 5.7 6.9    C=64 6.4 6.8   C=96 7.5 7.4
 //   asum 1024 chunks of L=64 C=128 11.5 12.1 C=256 17.3 18.6 C=384 23.4 22.9
 //   dot  64 chunks of L=16   C=32 5.9 6.2    C=64 6.7 6.2
+//        256 of L=16 C=64, 2 passes 7.1 6.6   360 8.7 7.5   512 7.4 7.6
 // and the two-step arrival of a 1-pass launch of 512 work-groups costs what
 // rows gain below 256 elements (asum, 512 chunks of L=64: C=128 12.0 13.3,
 // C=256 16.1 16.1).
 inline int rows_min_elems(const Plan& p, int rows, int64_t lanes) {
   if (rows == 32) return 384;
   if (p.passes == 1 && p.items * (p.L / rows) >= 2 * kRowsWaves * device_cus()) return 256;
-  return p.op == DPIA_OP_DOT && lanes <= 8 * device_cus() ? 64 : 96;
+  return p.op == DPIA_OP_DOT && lanes <= (p.passes == 1 ? 8 : 24) * device_cus() ? 64 : 96;
 }
 inline int rows_per_wave(const Plan& p) {
   if (p.order != DPIA_ORDER_CONTIGUOUS || p.dt != DPIA_F32 || p.nv != 4) return 0;

@@ -120,6 +120,12 @@ def test_contiguous_lanes_shorter_than_a_row_tile_stay_staged():
              for op in ("dot", "asum") for c, L, n in ((96, 16, 256), (128, 32, 64), (384, 64, 1000))]
     for call, l in first_kernels(rows):
         assert "rows" in l["kernel"], (call, l)
+    # (dots of few lanes from 64 elements: up to 8 lanes per compute unit in one
+    # pass, 24 in two)
+    for G, passes in ((128, (1, 2)), (129, (2,)), (384, (2,)), (385, ())):
+        calls = [("dot", dict(seq_len=64, local_size=16, passes=q, **C), dict(n=64 * 16 * G)) for q in (1, 2)]
+        for call, l in first_kernels(calls):
+            assert ("rows" in l["kernel"]) == (call[1]["passes"] in passes), (G, call, l)
 
 
 CODES = {dp.BF16: "GemvF32Acc<unsigned short, dpia::DecodeBF16, {e}, -1>",
