@@ -641,12 +641,13 @@ hipError_t launch_chunks(const Plan& p, const Op& op, const ReduceArgs& a, hipSt
   const bool can_split = a.nodes != nullptr;
   using Fed = typename BaseOp<Op>::type;
   if constexpr (Op::View::kStageable) {
-    // (loader wavefronts that take 64-lane chunks whole leave compute units
-    // idle: 3,000,000 elements, C=512 L=64: 27.4 us, 15.8 with 16 rows; Kahan's
-    // longer steps keep 64 lanes busy: 16.0 and 18.7 us at C=256)
+    // (Loader wavefronts take 64-lane chunks whole, but a last chunk in part is
+    // folded by one wavefront alone: 3,000,000 elements, C=512 L=64: 27.4 us,
+    // 15.8 with 16 rows; without such a chunk 2^20, C=256 L=64 8.0 and 10.8, asum
+    // of 2^21, C=512 8.3 and 12.5.  Kahan's chunks are whole.)
     const int per_wave = rows_per_wave(p);
     const int rows = fed_rows<Op::View::kOps>(p, can_split);
-    if (rows && !(rows == kWave && per_wave == 16 && FINAL == kFinalPlain) &&
+    if (rows && !(rows == kWave && per_wave == 16 && p.n % p.W != 0) &&
         (FINAL == kFinalPlain || (p.V == 1 && p.combine == DPIA_COMBINE_TREE)))
       return launch_fed<Fed, FINAL>(p, static_cast<const Fed&>(op), a, rows, stream);
     if (per_wave)

@@ -213,3 +213,13 @@ def test_chunks_of_long_strided_lanes_are_fed_whole_or_not():
              for r in (0, 1, 1024 * L - 1)]
     for call, l in first_kernels(calls):
         assert "fed_reduce_kernel" in l["kernel"], (call, l)
+
+
+def test_whole_contiguous_chunks_of_64_lanes_are_fed():
+    # a last chunk in part would be one wavefront's: 16 rows to a wavefront then
+    for op, C, Gs in (("dot", 256, (2, 64, 128, 255)), ("dot", 512, (129, 255)), ("asum", 512, (2, 64, 255))):
+        calls = [(op, dict(seq_len=C, local_size=64, passes=p, order=dp.CONTIGUOUS, wg_combine=dp.TREE),
+                  dict(n=64 * C * G - r)) for G in Gs for p in (1, 2) for r in (0, 1, 64 * C - 1)]
+        for call, l in first_kernels(calls):
+            whole = call[2]["n"] % (64 * C) == 0
+            assert ("fed_reduce_kernel" if whole else "rows_reduce_kernel") in l["kernel"], (call, l)
