@@ -570,7 +570,8 @@ hipError_t launch_gemv_rows(const Plan& p, const Op& op, int64_t m, int64_t lda,
 // with batches of 64 steps, as thin_plan (reduce.h) does for a dot.  Shorter
 // lanes are in flight whole with four of them to a thread (us, that and one to
 // a thread: 1024 rows of L=64, C=8 2.5 3.4, C=16 3.4 3.8, C=24 4.3 4.5, C=32
-// 4.8 4.4, C=64 7.9 6.3; 64 rows of L=32, C=32 3.4 3.6, C=48 4.8 4.3).
+// 4.8 4.4, C=64 7.9 6.3; 64 rows of L=16, C=24 3.7 3.4, C=32 4.5 3.5, C=40
+// 4.3 4.0; 256 of L=32, C=32 3.5 3.7).
 inline Plan gemv_thin_plan(const Plan& p, int64_t m) {
   Plan q = p;
   q.nv = 1;
@@ -589,9 +590,8 @@ inline Plan gemv_thin_plan(const Plan& p, int64_t m) {
 // (A bounded grid has to be large enough for work-groups of fewer than 256
 // threads: 4096 x 1024, C=64 L=16 under 300 work-groups 12.3 us, 8.5 not thin.)
 inline bool gemv_thin(const Plan& p, int64_t m) {
-  const int64_t lanes = m * p.L, cus = device_cus();
   if (p.order != DPIA_ORDER_STRIDED || p.nv != 4 || p.team < 4 || p.L > 256 ||
-      lanes > 256 * cus || p.C < (lanes < 16 * cus ? 48 : 32))
+      m * p.L > 256 * static_cast<int64_t>(device_cus()) || p.C < 32)
     return false;
   const Plan q = gemv_thin_plan(p, m);
   return q.wg_threads >= 256 || !grid_is_bound(q, (m + q.teams_per_wg - 1) / q.teams_per_wg);
