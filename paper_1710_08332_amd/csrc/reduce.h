@@ -6,10 +6,16 @@
 // value is written to the workspace, partial[g] (the hoisted newGlobal
 // temporary of Sec. 6.3: one slot per parforWorkgroup iteration).  The outer
 // reduceSeq over partial[0..G) from +0 in chunk order then runs either in a
-// second kernel (2 passes) or in the last work-group to finish (1 pass:
-// device-coherent chunk-value stores, an integer arrival counter, coherent
-// loads in the last work-group).  Both evaluate the same expression and give
-// the same bits.
+// second kernel (2 passes) or in the last work-group to finish (1 pass).  Both
+// evaluate the same expression and give the same bits.
+//
+// 1 pass: every thread stores its chunk values device-coherently, waits until
+// they are in memory, and meets the work-group at a barrier; then one thread
+// counts the work-group's arrival (relaxed, last_to_arrive) and a second
+// barrier hands its answer on.  The last work-group reads few values with
+// device-coherent loads; where there are more, every wavefront that reads does
+// an agent-scope acquire first and loads plainly (final_fold).  No work-group
+// writes its L2 back.
 #pragma once
 
 #include <type_traits>
@@ -41,8 +47,6 @@ struct ReduceArgs {
   void* out;
 };
 
-// MAXT: the largest work-group it is launched with (256 or 1024); the
-// 256-thread build may use more registers than the 1024-thread one.
 // The arrival of a 1-pass work-group (one thread calls this, when all of the
 // work-group's chunk values are in memory): true for the last one of the
 // launch.  The counter is left at zero.
@@ -69,6 +73,8 @@ __device__ __forceinline__ bool last_to_arrive(unsigned int* counter) {
 }
 
 // STAGED: the contiguous order through LDS (see chunk_value).
+// MAXT: the largest work-group it is launched with (256 or 1024); the
+// 256-thread build may use more registers than the 1024-thread one.
 template <class Op, int ORDER, int NV, int COMBINE, int FINAL, int VEC, int MAXT, bool STAGED>
 __global__ void __launch_bounds__(MAXT) reduce_kernel(Op op, ReduceArgs a) {
   using T = typename Op::T;
@@ -102,11 +108,8 @@ __global__ void __launch_bounds__(MAXT) reduce_kernel(Op op, ReduceArgs a) {
     }
   }
   if (a.one_pass) {
-    // Chunk values were written with device-coherent stores; each thread
-    // waits for its own to complete, the barrier then puts all of this
-    // work-group's before the arrival counter, and the last work-group to
-    // arrive reads them back with device-coherent loads.  No L2 write-back
-    // per work-group.
+    // (the protocol at the head of this file: own stores in memory, barrier,
+    // arrival, barrier)
     wait_memory();
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -432,7 +435,8 @@ int fed_rows(const Plan& p, bool can_split) {
 //   dot  2^26 C=256 L=64 (262,144)   99.9  101    asum 50.7 47.9
 //   dot  2^26 C=64 L=64 (2^20)       127   116    asum 60.0 50.3
 // Hence up to 256 lanes per compute unit; an asum, with one operand to keep
-// in flight, also up to 512, and with a wavefront per chunk (L = 64) always.
+// in flight, also up to 512, and with a wavefront per chunk (L = 64) beyond
+// (2 passes: C=16 2^26 69.1 68.6, 2^24 21.5 19.6; 1 pass: see below).
 // Lanes that not even `nv` to a thread make a team of 256 threads are left to
 // the plan as it is, with the operation's own batches: 64 steps of two lanes
 // are 128 registers of loads, all that a thread of a larger work-group has
