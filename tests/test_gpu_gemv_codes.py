@@ -68,3 +68,14 @@ def test_strided_rows_outside_the_blocks(dt, L, C, short):
 def test_contiguous_rows(dt, L, C, short):
     s = dp.Strategy(seq_len=C, local_size=L, wg_combine=dp.TREE if L & (L - 1) == 0 else dp.SEQ)
     check(dt, 41, L * C - short, s)
+
+
+@pytest.mark.parametrize("dt,w", [(dp.BF16, w) for w in (100, 3000, 16500)] +
+                         [(dp.FP8_E4M3, w) for w in (100, 1700, 2300, 9000)])
+@pytest.mark.parametrize("team", (1, 2, 3, 4, 24, 64, 256))
+@pytest.mark.parametrize("parts", (1, 2))
+def test_rows_combined_one_after_the_other(dt, w, team, parts):
+    # a thread to each of a team's 1, 2 or 4 rows, more rows than threads among them
+    L = team * (8 if dt == dp.BF16 else 16)
+    s = dp.Strategy(seq_len=2, local_size=L, order=dp.STRIDED, wg_combine=dp.SEQ, row_parts=parts)
+    check(dt, w * 64 // team + 1, 2 * L * parts - L - 3, s)

@@ -222,3 +222,20 @@ def test_whole_contiguous_chunks_of_64_lanes_are_fed():
         for call, l in first_kernels(calls):
             whole = call[2]["n"] % (64 * C) == 0
             assert ("fed_reduce_kernel" if whole else "rows_reduce_kernel") in l["kernel"], (call, l)
+
+
+def test_row_blocks_hold_all_rows_of_a_sequential_combine():
+    calls, need = [], []
+    for dt, nv, ws in ((dp.BF16, 8, (100, 3000, 16500)), (dp.FP8_E4M3, 16, (100, 1700, 2300, 9000))):
+        for w in ws:
+            for team in (1, 2, 3, 4, 24, 63, 64, 128, 255, 256):
+                for g in (0, 70):
+                    calls.append(("gemv", dict(seq_len=2, local_size=team * nv, order=dp.STRIDED,
+                                               wg_combine=dp.SEQ, max_grid=g),
+                                  dict(dtype=dt, m=w * 64 // team + 1, k=2 * team * nv)))
+                    need.append((team, nv))
+    for (call, l), (team, nv) in zip(first_kernels(calls), need):
+        rows = int(l["kernel"].split(">(")[0].rsplit(",", 1)[1])
+        assert f", {nv}, 1, {rows}>" in l["kernel"] and l["block"] % team == 0, (call, l)
+        # (a row's lanes and a slot for its first part)
+        assert l["block"] // team * rows * (team * nv + 1) * 4 <= l["lds"] <= 160 * 1024, (call, l)
