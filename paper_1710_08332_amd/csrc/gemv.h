@@ -200,8 +200,8 @@ __device__ __forceinline__ float lanes_in_turn(const float* lanes, int L) {
 // A sequential combine of one row is a chain of L additions that one thread
 // does while its wavefront waits, so the rows of a team are combined side by
 // side, a thread each (us, row after row and so; a work-group of 256 threads
-// with 2 rows: fp8 6800 x 6656, C=13 L=512 52.9 19.32, 39.3; 20000 x 16384, C=32
-// L=512 165 82.53, 97.3; bf16 17000 x 16384, C=32 L=512 137 103.8, 118).
+// with 2 rows: fp8 6800 x 6656, C=13 L=512 52.9 19.3, 39.3; 20000 x 16384, C=32
+// L=512 165 82.5, 97.3; bf16 17000 x 16384, C=32 L=512 137 104, 118).
 template <class Op, int NV, int COMBINE, int RB>
 __global__ void __launch_bounds__(256) gemv_block_kernel(Op op, GemvArgs a) {
   using T = float;

@@ -75,12 +75,26 @@ bool gemv_halves(const Plan& p, int64_t m) {
 //              C=16   4600         --    23.2  23.5  20.2
 //        L=256 C=64   4000         81.1  61.3  55.9  72.6   8000  --  120  108  125
 //        L=64  C=16   12000        --    50.7  47.9  59.6
+// and with many wavefronts (S: work-groups of 256 threads, 2 rows x 16):
+//  bf16  L=256 C=32   16500 waves  S 93.3  2x16 82.3  4x16 91.7   33000  S 182  158  166
+//        L=512 C=8    20480        S 29.3  27.3  28.7             50000  S 68.3  62.3  61.3
+//        L=512 C=32   16384        S 91.6  85.0  83.4             16500  S 92.9  85.3  90.3
+//              C=16   21000        S 54.9  56.5  55.4             50000  S 136   130   120
+//  fp8   L=512 C=24   9000 waves   S 54.5  4x64 49.3  4x16 60.7   13000  S 81.1  65.4  69.8
+//              C=24   16384        S 90.1  79.0  79.1             17000  S 88.7  84.1  98.2
+//              C=33   11000        S 75.0  68.8  78.1             13000  S 101   88.7  82.5
+//              C=33   16384        S 111   101   89.2             30000  S 208   181   169
+//        L=64  C=5    5000         S 33.2  31.8  26.4             8000   S 39.1  37.0  44.8
+//        L=128 C=16   10000        S 36.5  35.8  38.3             16384  S 57.8  54.7  47.0
 // Hence: bf16 1x64 up to 8 wavefronts per compute unit (6 with 64 threads to a
-// team), 2x16 up to 64, 4x16; fp8 1x64 up to 6, 2x64 up to 8, 4x64 up to 16,
-// then 4x16, but 4x64 for narrow teams and for long lanes where it wins.  (With
-// 256-thread work-groups, 2 rows and 16 elements, the bf16 launches of 2048 and
-// 3000 wavefronts above took 12.3, 13.7, 32.2, 39.2, 18.7 and 21.2 us; the fp8
-// ones, of 2 or 4 rows, 34.6, 36.0, 40.0, 37.9, 65.5, 20.2, 82.7, 155 and 51.3.)
+// team), then 2x16; 4x16 for teams of 64 threads with lanes of 13 and more, from
+// 80 on, and at 64, where the launch is one round of what is resident.  fp8 1x64
+// up to 6, 2x64 up to 8, 4x64 up to 16, then 4x16; but 4x64 for narrow teams of
+// long lanes, and where 4x16 would just begin on another wavefront per SIMD (32
+// to 44 or 48, 64 to 72).  (With 256-thread work-groups, 2 rows and 16 elements, the
+// bf16 launches of 2048 and 3000 wavefronts above took 12.3, 13.7, 32.2, 39.2,
+// 18.7 and 21.2 us; the fp8 ones, of 2 or 4 rows, 34.6, 36.0, 40.0, 37.9, 65.5,
+// 20.2, 82.7, 155 and 51.3.)
 // (a bounded grid: 2 bf16 rows instead of 4, 2 fp8 rows instead of 1, as the
 // work-groups of launch_gemv_block are large then)
 int64_t block_waves(const Plan& p, int64_t m) { return (m * p.team + kWave - 1) / kWave; }
@@ -88,7 +102,8 @@ int64_t block_waves(const Plan& p, int64_t m) { return (m * p.team + kWave - 1) 
 hipError_t launch_bf16(const Plan& p, const GemvBF16& op, int64_t m, int64_t lda, hipStream_t s) {
   if (!gemv_blocks<GemvBF16>(p)) return launch_gemv<GemvBF16, 8>(p, op, m, lda, s);
   const int64_t waves = block_waves(p, m), cus = device_cus();
-  if (waves >= 64 * cus && !grid_is_bound(p, waves / 4))
+  const bool whole = waves > 62 * cus && waves <= 64 * cus;   // one round of 4 rows
+  if (p.team >= kWave && p.C >= 13 && (waves >= 80 * cus || whole) && !grid_is_bound(p, waves / 4))
     return launch_gemv_block<GemvBF16, 4>(p, op, m, lda, s);
   if (waves > (p.team >= kWave ? 6 : 8) * cus)
     return launch_gemv_block<GemvBF16, 2>(p, op, m, lda, s);
@@ -104,8 +119,12 @@ hipError_t launch_fp8(const Plan& p, const GemvFP8& op, int64_t m, int64_t lda, 
   }
   const int64_t waves = block_waves(p, m), cus = device_cus();
   if (waves > 8 * cus) {
-    const bool deep4 = waves <= 16 * cus || p.team <= 4 || (p.C >= 64 && p.team <= 16) ||
-                       (waves > 32 * cus && p.C >= 32 && (p.team <= 16 || waves < 56 * cus));
+    const bool many = waves > 32 * cus, narrow = p.team <= 16;
+    const bool deep4 = waves <= 16 * cus || (p.C >= 64 && narrow) ||
+                       (p.team <= 4 && (p.C >= 16 || waves > 24 * cus)) ||
+                       (many && p.C >= 32 && (narrow || waves <= 48 * cus)) ||
+                       (many && p.C >= 16 && p.team <= 32 && waves <= (p.C >= 18 ? 48 : 44) * cus) ||
+                       (p.C >= 18 && waves > 64 * cus && waves <= 72 * cus);
     if (deep4) return launch_gemv_block<GemvFP8Deep, 4>(p, deep, m, lda, s);
     return launch_gemv_block<GemvFP8, 4>(p, op, m, lda, s);
   }

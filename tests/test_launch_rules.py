@@ -134,15 +134,24 @@ CODES = {dp.BF16: "GemvF32Acc<unsigned short, dpia::DecodeBF16, {e}, -1>",
 # per team, elements per batch (0: 16)
 BLOCK_LINES = [
     (dp.BF16, 1536, 17, 512, 1, 64), (dp.BF16, 1537, 17, 512, 2, 0), (dp.BF16, 4096, 17, 256, 1, 64),
-    (dp.BF16, 4097, 17, 256, 2, 0), (dp.BF16, 16383, 17, 512, 2, 0), (dp.BF16, 16384, 17, 512, 4, 0),
+    (dp.BF16, 4097, 17, 256, 2, 0), (dp.BF16, 15872, 17, 512, 2, 0), (dp.BF16, 15873, 17, 512, 4, 0),
+    (dp.BF16, 16384, 17, 512, 4, 0), (dp.BF16, 16385, 17, 512, 2, 0), (dp.BF16, 20479, 13, 512, 2, 0),
+    (dp.BF16, 20480, 13, 512, 4, 0), (dp.BF16, 20480, 12, 512, 2, 0), (dp.BF16, 40960, 17, 256, 2, 0),
     (dp.FP8_E4M3, 3072, 17, 512, 1, 64), (dp.FP8_E4M3, 3074, 17, 512, 2, 64),
     (dp.FP8_E4M3, 4096, 17, 512, 2, 64), (dp.FP8_E4M3, 4098, 17, 512, 4, 64),
     (dp.FP8_E4M3, 8192, 15, 512, 4, 64), (dp.FP8_E4M3, 8194, 19, 512, 4, 0),
     (dp.FP8_E4M3, 65552, 17, 64, 4, 64), (dp.FP8_E4M3, 32776, 17, 128, 4, 0),
     (dp.FP8_E4M3, 16388, 63, 256, 4, 0), (dp.FP8_E4M3, 16388, 64, 256, 4, 64),
     (dp.FP8_E4M3, 32768, 32, 256, 4, 0), (dp.FP8_E4M3, 32772, 32, 256, 4, 64),
-    (dp.FP8_E4M3, 32772, 31, 256, 4, 0), (dp.FP8_E4M3, 28670, 33, 512, 4, 64),
-    (dp.FP8_E4M3, 28672, 33, 512, 4, 0),
+    (dp.FP8_E4M3, 16386, 15, 512, 4, 0), (dp.FP8_E4M3, 16386, 16, 512, 4, 64),
+    (dp.FP8_E4M3, 22528, 17, 512, 4, 64), (dp.FP8_E4M3, 22530, 17, 512, 4, 0),
+    (dp.FP8_E4M3, 8194, 17, 1024, 4, 0), (dp.FP8_E4M3, 24576, 33, 512, 4, 64),
+    (dp.FP8_E4M3, 24578, 33, 512, 4, 0), (dp.FP8_E4M3, 32768, 18, 512, 4, 0),
+    (dp.FP8_E4M3, 24576, 18, 512, 4, 64), (dp.FP8_E4M3, 24578, 18, 512, 4, 0),
+    (dp.FP8_E4M3, 65552, 15, 64, 4, 0), (dp.FP8_E4M3, 98304, 15, 64, 4, 0),
+    (dp.FP8_E4M3, 98320, 15, 64, 4, 64),
+    (dp.FP8_E4M3, 32770, 18, 512, 4, 64), (dp.FP8_E4M3, 36864, 18, 512, 4, 64),
+    (dp.FP8_E4M3, 36866, 18, 512, 4, 0),
 ]
 
 
