@@ -160,7 +160,8 @@ __global__ void __launch_bounds__(64)
                       const float* partials) {
   extern __shared__ __align__(16) float lds[];
   const BInst I = insts[red[blockIdx.x]];
-  final_fold<PlainF32, kFinalPlain>(partials + I.part_off, I.G, I.out, 0, lds);
+  final_fold<PlainF32, kFinalPlain>(partials + I.part_off, I.G, I.out, 0, lds,
+                                            I.op != DPIA_OP_ASUM);
 }
 
 // One launch.  `arrive`: one counter per instance, zero between runs.
@@ -210,7 +211,8 @@ __global__ void __launch_bounds__(kBatchThreads)
       // complete in memory; fold them in chunk order (the fold's own
       // barriers also free its LDS before the next tile)
       const BInst I = insts[fold];
-      final_fold<PlainF32, kFinalPlain, true>(partials + I.part_off, I.G, I.out, 0, lds);
+      final_fold<PlainF32, kFinalPlain, true>(partials + I.part_off, I.G, I.out, 0, lds,
+                                            I.op != DPIA_OP_ASUM);
       if (threadIdx.x == 0)
         __hip_atomic_store(arrive + fold, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

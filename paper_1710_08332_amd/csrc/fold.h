@@ -192,20 +192,6 @@ __device__ __forceinline__ F walk_lanes(const F (&v)[E], F cur, int lanes, int l
   return cur;
 }
 
-// Whether the wavefront holds values of both signs.
-template <class F, int E>
-__device__ __forceinline__ bool both_signs(const F (&v)[E]) {
-  using U = typename FoldBits<F>::U;
-  U any = 0, all = ~U(0);
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    any |= to_bits(v[j]);
-    all &= to_bits(v[j]);
-  }
-  constexpr int kSign = sizeof(F) * 8 - 1;
-  return __ballot((any >> kSign) != 0) != 0 && __ballot((all >> kSign) == 0) != 0;
-}
-
 // A wavefront with more changes of binade than this, or whose starts fail
 // step 5 more often than this, is folded lane by lane: a stop costs about 30
 // instructions, a lane of walk_lanes 20.
@@ -235,10 +221,10 @@ __device__ __forceinline__ int fold_thread() {
 // values (w * 64 + l) * E ..., zeros past the `lanes` lanes (of the first
 // `waves` wavefronts) that hold any.  Every thread of the work-group calls
 // this; acc ends as the chain's value in all of them, and `start` as the
-// calling lane's start.  `only`: these are all values of the fold.
+// calling lane's start.  `walk`: a single wavefront folds its lanes in turn.
 template <bool START, class F, int E>
 __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, int waves,
-                                            F* slots, F& start, bool only) {
+                                            F* slots, F& start, bool walk) {
   using U = typename FoldBits<F>::U;
   constexpr int kMant = FoldBits<F>::kMantissa;
   const int tid = fold_thread();
@@ -252,9 +238,7 @@ __device__ __forceinline__ void block_chain(const F (&v)[E], F& acc, int lanes, 
   F incl = F(0), own = F(0);
   bool in_turn = false;                          // lane by lane
   if (mine) {
-    // (one wavefront's values are all there are, of both signs: few lanes keep
-    // their binade, and what comes before the walk would be in vain)
-    if constexpr (!START) in_turn = only && waves == 1 && both_signs(v);
+    in_turn = walk && waves == 1;
     if (!in_turn) {
       own = fold_lane(v, F(0));
       incl = wave_prefix(own);
@@ -356,20 +340,28 @@ static_assert(kFoldSlots * sizeof(double) <= kFoldLds, "the plan reserves the fo
 // invalidates the compute unit's cache, which the other work-groups there go on
 // using: with one for each of the 3,000 small folds of a one-launch batch it
 // took 36 us, not 24.
+// `signs`: the values may be of both signs.  Where one wavefront holds them all,
+// their sum leaves its binade in most lanes then, and they are folded lane by
+// lane (a dot's 513 to 900 values after the chunks' launch: scanned 8.4 to 9.8
+// us a call, in turn 7.1 to 8.9, one by one 7.0 to 9.0); an asum's grows through
+// a few binades (1,024 values: scanned 6.0, one by one 7.8).
 template <class A, int FINAL, bool COHERENT = false>
 __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_t G, void* out,
-                           int out_f64, void* lds) {
+                           int out_f64, void* lds, bool signs) {
   using T = typename A::T;
   constexpr int E = kFoldLaneValues<T>;
-  // fewer values than this many lanes hold are folded lane by lane
+  // Up to this many lanes are folded lane by lane, from `signs` up to all (not
+  // the pairs' binary32 chain, whose steps are ten instructions).
   constexpr int kFewLanes = 32;
+  constexpr bool kPairs = FINAL == kFinalKahan32 || FINAL == kFinalSum2_32;
   const int tid = fold_thread();
   int whole = static_cast<int>(blockDim.x) / kWave;   // wavefronts without missing threads
   whole = whole < kFoldWaves ? whole : kFoldWaves;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const bool few = !std::is_integral_v<T> && G <= kFewLanes * E;
-  const bool reads = std::is_integral_v<T> ? wave * kWave < G : !few;
+  const bool turns = G <= (signs && !kPairs ? kWave : kFewLanes) * E;
+  const bool reads = std::is_integral_v<T> ? wave * kWave < G : !few && (wave == 0 || !turns);
   if constexpr (COHERENT) {
     if (reads) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
@@ -396,10 +388,21 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
     T acc = A::zero();
     double acc64 = 0.0;
     T v[E] = {};
-    // this lane's values of the block at b (zeros past the end)
-    auto load = [&](int64_t b) {
+    // this lane's values of the block at b (zeros past the end); one by one,
+    // coherently, where ONE
+    auto load = [&](int64_t b, auto one) {
+      constexpr bool ONE = decltype(one)::value;
       const int64_t at = b + (static_cast<int64_t>(wave) * kWave + lane) * E;
-      if (at + E <= G && !(COHERENT && few)) {
+      if constexpr (ONE) {
+        // (past the end the last value is read again: no branch, and no wait,
+        // between the loads)
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = load_coherent(partials + (at + j < G ? at + j : G - 1));
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[j] = at + j < G ? v[j] : A::zero();
+        return E;
+      }
+      if (at + E <= G) {
         __builtin_memcpy(v, partials + at, sizeof(v));
         return E;
       }
@@ -408,7 +411,7 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
       for (int j = 0; j < E; ++j) {
         v[j] = A::zero();
         if (at + j < G) {
-          v[j] = COHERENT && few ? load_coherent(partials + at + j) : partials[at + j];
+          v[j] = partials[at + j];
           ++n;
         }
       }
@@ -422,9 +425,12 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
       else
         return 0.0;
     };
-    if (G <= kFewLanes * E) {
+    if (turns) {
       if (wave == 0) {
-        load(0);
+        if (COHERENT && few)
+          load(0, std::bool_constant<COHERENT>{});
+        else
+          load(0, std::false_type{});
         const int lanes = static_cast<int>((G + E - 1) / E);
         if constexpr (k64) {
           double w[E];
@@ -448,21 +454,20 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
       }
     } else {
       const int64_t block = static_cast<int64_t>(whole) * kWave * E;
-      const bool only = G <= block;
       for (int64_t b = 0; b < G; b += block) {
         const int64_t left = G - b < block ? G - b : block;
         const int lanes = static_cast<int>((left + E - 1) / E);
         const int waves = (lanes + kWave - 1) / kWave;
         int n = 0;
-        if (wave < waves) n = load(b);
+        if (wave < waves) n = load(b, std::false_type{});
         if constexpr (k64) {
           double w[E], start;
 #pragma unroll
           for (int j = 0; j < E; ++j) w[j] = value64(v[j]);
-          block_chain<false>(w, acc64, lanes, waves, static_cast<double*>(lds), start, only);
+          block_chain<false>(w, acc64, lanes, waves, static_cast<double*>(lds), start, false);
         } else if constexpr (sizeof(T) == 4) {
           float start;
-          block_chain<false>(v, acc, lanes, waves, static_cast<float*>(lds), start, only);
+          block_chain<false>(v, acc, lanes, waves, static_cast<float*>(lds), start, false);
         } else {
           // pairs: the s parts are a chain of their own; from its running
           // values come the exact errors, and the c parts are a chain over
@@ -470,7 +475,7 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
           float s[E], w[2 * E], start = 0.0f, cstart;
 #pragma unroll
           for (int j = 0; j < E; ++j) s[j] = v[j].s;
-          block_chain<true>(s, acc.s, lanes, waves, static_cast<float*>(lds), start, only);
+          block_chain<true>(s, acc.s, lanes, waves, static_cast<float*>(lds), start, false);
           T l{start, 0.0f};
 #pragma unroll
           for (int j = 0; j < E; ++j) {
@@ -480,7 +485,8 @@ __device__ __forceinline__ void final_fold(const typename A::T* partials, int64_
             w[2 * j + 1] = j < n ? t.c : 0.0f;
             l = t;
           }
-          block_chain<false>(w, acc.c, lanes, waves, static_cast<float*>(lds), cstart, only);
+          // (the errors are of both signs)
+          block_chain<false>(w, acc.c, lanes, waves, static_cast<float*>(lds), cstart, G <= block);
         }
       }
     }

@@ -88,6 +88,7 @@ struct DotF32Deeper : DotF32 {
 // batch keeps the same bytes in flight (measured at 2^26, C=256 L=1024:
 // 69% -> 83% of peak).
 struct AsumF32 {
+  static constexpr bool kOneSign = true;   // its chunk values
   static constexpr int kBatchElems = 2 * DPIA_BATCH_ELEMS;
   using Arith = PlainF32;
   using T = float;
@@ -166,6 +167,11 @@ template <class Op>
 struct OneLane : Op {
   static constexpr int kBatchSteps = 64;
 };
+// Whether an operation's chunk values are of one sign.
+template <class Op, class = void>
+constexpr bool one_sign = false;
+template <class Op>
+constexpr bool one_sign<Op, decltype(void(Op::kOneSign))> = Op::kOneSign;
 template <class Op, class = void>
 struct BaseOp {
   using type = Op;

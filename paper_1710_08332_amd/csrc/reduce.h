@@ -117,7 +117,8 @@ __global__ void __launch_bounds__(MAXT) reduce_kernel(Op op, ReduceArgs a) {
     }
     __syncthreads();
     if (is_last) {
-      final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds);
+      final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds,
+                                                  !one_sign<Op>);
     }
   }
 }
@@ -219,7 +220,8 @@ __global__ void __launch_bounds__(kWave*(1 + kFedLoaders)) fed_reduce_kernel(Op 
     }
     __syncthreads();
     if (is_last) {
-      final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds);
+      final_fold<typename Op::Arith, FINAL, true>(partials, a.values, a.out, a.out_f64, lds,
+                                                  !one_sign<Op>);
     }
   }
 }
@@ -283,15 +285,15 @@ __global__ void __launch_bounds__(kWave* kRowsWaves) rows_reduce_kernel(Op op, R
     if (threadIdx.x == 0) is_last = last_to_arrive(a.counter);
     __syncthreads();
     if (is_last)
-      final_fold<A, FINAL, true>(partials, a.values, a.out, a.out_f64, lds_raw);
+      final_fold<A, FINAL, true>(partials, a.values, a.out, a.out_f64, lds_raw, !one_sign<Op>);
   }
 }
 
 template <class A, int FINAL>
 __global__ void __launch_bounds__(1024) final_kernel(const typename A::T* partials, int64_t G,
-                                                     void* out, int out_f64) {
+                                                     void* out, int out_f64, int signs) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  final_fold<A, FINAL>(partials, G, out, out_f64, lds_raw);
+  final_fold<A, FINAL>(partials, G, out, out_f64, lds_raw, signs != 0);
 }
 
 template <class Op>
@@ -691,7 +693,8 @@ hipError_t launch_fold(int64_t G, const void* partials, void* out, int out_f64,
                        hipStream_t stream) {
   using T = typename Op::T;
   const T* pp = static_cast<const T*>(partials);
-  void* args[] = {&pp, &G, &out, &out_f64};
+  int signs = !one_sign<Op>;
+  void* args[] = {&pp, &G, &out, &out_f64, &signs};
   auto kern = final_kernel<typename Op::Arith, FINAL>;
   const int threads = G > 4 * kWave * kFoldLaneValues<T> ? 1024 : 256;
   return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(1), dim3(threads), args,

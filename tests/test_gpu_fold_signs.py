@@ -1,7 +1,8 @@
-"""Folds whose values are all held by one wavefront, where the signs decide
-between the walk and the scan: one sign, the other, one value of the other
-sign at either end, zeros of both signs.  Against the additions one by one,
-bit for bit."""
+"""Folds whose values are all held by one wavefront: from 513 values on a dot's
+go lane by lane, an asum's are scanned.  One sign, the other, one value of the
+other sign at either end, zeros of both signs, and the last work-group of a
+launch with few and more values.  Against the additions one by one, bit for
+bit."""
 
 import numpy as np
 import pytest
@@ -11,6 +12,7 @@ pytestmark = pytest.mark.gpu
 
 import paper_1710_08332_amd as dp  # noqa: E402
 from tests.test_gpu_fold import F, pairs, plain, same, values  # noqa: E402
+from tests.test_gpu_thin import run  # noqa: E402
 
 
 def signed(kind, n):
@@ -29,12 +31,20 @@ def signed(kind, n):
 
 
 @pytest.mark.parametrize("kind", ("positive", "negative", "first", "last", "minus zeros", "mixed"))
-@pytest.mark.parametrize("n", (513, 600, 1008, 1024, 1025))
-def test_plain(kind, n):
+@pytest.mark.parametrize("op", (dp.OP_DOT, dp.OP_ASUM))
+@pytest.mark.parametrize("n", (511, 512, 513, 600, 1008, 1023, 1024, 1025))
+def test_plain(kind, op, n):
     v = signed(kind, n)
     s = dp.Strategy(seq_len=4, local_size=1, wg_combine=dp.SEQ)
-    got = dp.fold(dp.OP_DOT, s, torch.from_numpy(v).cuda(), 4 * n, dp.F32)
-    same(got.cpu().numpy(), plain(v), (kind, n))
+    got = dp.fold(op, s, torch.from_numpy(v).cuda(), 4 * n, dp.F32)
+    same(got.cpu().numpy(), plain(v), (kind, op, n))
+
+
+@pytest.mark.parametrize("op", ("dot", "asum"))
+@pytest.mark.parametrize("G", (1, 15, 16, 17, 511, 512, 513, 1023, 1024, 1025))
+def test_last_work_group(op, G):
+    run(op, 3 * 16 * G, dp.Strategy(seq_len=3, local_size=16, order=dp.STRIDED, wg_combine=dp.TREE,
+                                    passes=1), 7)
 
 
 @pytest.mark.parametrize("kind", ("positive", "first", "mixed"))
