@@ -52,10 +52,14 @@ namespace {
 // whole batches leave it without loads while it folds (us, before and now:
 // 8192^2 C=64 L=128 49.8, 42.4, C=128 L=64 46.7, 43.9; 16384^2 C=128 L=128
 // 168.6, 154.9, C=256 L=64 168.1, 162.7; but 8192^2 C=32 L=256 42.7, 44.2,
-// 16384^2 C=512 L=32 160.5, 166.6, 3432 x 15745 C=124 L=128 37.4, 38.5).
+// 16384^2 C=512 L=32 160.5, 166.6).  16 wavefronts are resident per compute
+// unit; with fewer the one row of each is too little, most of all where they
+// begin on another wavefront per SIMD (speed against gemv_kernel, C=64 L=128 and
+// C=128 L=64: 2300 wavefronts 0.89 0.99, 2560 0.87 0.98, 3584 0.96 1.00, 3900
+// 1.00 1.03, 4096 1.09 1.22, 9000 1.09 1.15, 16384 1.05 1.13).
 bool gemv_halves(const Plan& p, int64_t m) {
   return gemv_blocks<GemvF32>(p) && (p.L == 64 || p.L == 128) && p.C >= 64 &&
-         m * p.team >= 8 * kWave * static_cast<int64_t>(device_cus()) &&
+         m * p.team >= 15 * kWave * static_cast<int64_t>(device_cus()) &&
          !grid_is_bound(p, m * p.team / kWave);
 }
 

@@ -164,6 +164,15 @@ def test_row_blocks_of_codes():
         assert want in l["kernel"], (call, l)
 
 
+def test_strided_rows_in_halves_need_sixteen_wavefronts_per_compute_unit():
+    for L in (64, 128):
+        for waves, halves in ((2048, False), (3584, False), (3839, False), (3840, True), (9000, True)):
+            calls = [("gemv", dict(seq_len=C, local_size=L, order=dp.STRIDED), dict(m=waves * 256 // L, k=L * C))
+                     for C in (64, 100)]
+            for call, l in first_kernels(calls):
+                assert ("gemv_block_kernel" in l["kernel"]) == halves, (waves, call, l)
+
+
 def test_fp8_rows_outside_the_blocks_have_deep_batches_where_lanes_are_long():
     # (lanes no 16 of which are whole, contiguous rows, teams of more than 256)
     for C, e in ((63, 0), (64, 64), (171, 64)):
