@@ -69,6 +69,7 @@ bool gemv_halves(const Plan& p, int64_t m) {
 // Measured with 64-thread work-groups (us; rows per team x elements per batch):
 //  bf16  L=256 C=16   2048 waves   1x64 11.7  2x16 11.9     3000  19.8  13.5
 //              C=64   2048         27.1  31.0               3000  43.0  35.6
+//        L=16  C=3, two parts 300 waves 5.5 4.6
 //        L=512 C=32   1024         11.7  15.4  2048  18.9  17.6  3000  32.2  21.0
 //              C=32   8000         66.5  50.5  4x16 49.4   16384  131  96.5  96.5
 //  fp8   L=512 C=32   1400 waves   1x64 20.6  2x64 17.2  4x64 24.0  4x16 33.6
@@ -91,7 +92,7 @@ bool gemv_halves(const Plan& p, int64_t m) {
 //        L=64  C=5    5000         S 33.2  31.8  26.4             8000   S 39.1  37.0  44.8
 //        L=128 C=16   10000        S 36.5  35.8  38.3             16384  S 57.8  54.7  47.0
 // Hence: bf16 1x64 up to 8 wavefronts per compute unit (6 with 64 threads to a
-// team), then 2x16; 4x16 for teams of 64 threads with lanes of 13 and more, from
+// team; 1 where lanes of fewer than 8 elements have no deep batch), then 2x16; 4x16 for teams of 64 threads with lanes of 13 and more, from
 // 80 on, and at 64, where the launch is one round of what is resident.  fp8 1x64
 // up to 6, 2x64 up to 8, 4x64 up to 16, then 4x16; but 4x64 for narrow teams of
 // long lanes, and where 4x16 would just begin on another wavefront per SIMD (32
@@ -109,7 +110,7 @@ hipError_t launch_bf16(const Plan& p, const GemvBF16& op, int64_t m, int64_t lda
   const bool whole = waves > 62 * cus && waves <= 64 * cus;   // one round of 4 rows
   if (p.team >= kWave && p.C >= 13 && (waves >= 80 * cus || whole) && !grid_is_bound(p, waves / 4))
     return launch_gemv_block<GemvBF16, 4>(p, op, m, lda, s);
-  if (waves > (p.team >= kWave ? 6 : 8) * cus)
+  if (waves > (p.C < 8 ? 1 : (p.team >= kWave ? 6 : 8)) * cus)
     return launch_gemv_block<GemvBF16, 2>(p, op, m, lda, s);
   const GemvBF16Deep deep{op.A, op.x, op.scale, op.y, op.blas, op.beta_zero, op.alpha, op.beta};
   return launch_gemv_block<GemvBF16Deep, 1>(p, deep, m, lda, s);

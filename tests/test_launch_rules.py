@@ -133,6 +133,7 @@ CODES = {dp.BF16: "GemvF32Acc<unsigned short, dpia::DecodeBF16, {e}, -1>",
 # (matrix type, rows, elements of a lane, lanes) where the launch changes: rows
 # per team, elements per batch (0: 16)
 BLOCK_LINES = [
+    (dp.BF16, 8192, 7, 16, 1, 64), (dp.BF16, 8193, 7, 16, 2, 0), (dp.BF16, 8193, 8, 16, 1, 64),
     (dp.BF16, 1536, 17, 512, 1, 64), (dp.BF16, 1537, 17, 512, 2, 0), (dp.BF16, 4096, 17, 256, 1, 64),
     (dp.BF16, 4097, 17, 256, 2, 0), (dp.BF16, 15872, 17, 512, 2, 0), (dp.BF16, 15873, 17, 512, 4, 0),
     (dp.BF16, 16384, 17, 512, 4, 0), (dp.BF16, 16385, 17, 512, 2, 0), (dp.BF16, 20479, 13, 512, 2, 0),
