@@ -566,6 +566,8 @@ __global__ void __launch_bounds__(kWave* kRowsWaves) gemv_rows_kernel(Op op, Gem
 //   8192^2       C=32 L=512             160  77      16384^2 C=32 L=512 625 225
 // (8192 x 1000 under C=32 L=512, where 32 of a row's 512 lanes have elements,
 // 43 and 49 us: rows much shorter than their lanes stay with gemv_kernel.)
+// (32 rows take tiles of 64 elements: 759 x 1276, C=32 L=64, 4.0 4.6; C=64 is 9%
+// faster in the mean.)
 // A row tile is 128 elements of 16 rows, so lanes shorter than 96 mostly load
 // nothing: rows win there only where the launch is small, or where the row's
 // length is no multiple of 4 and gemv_kernel's last parts are loaded one by one
@@ -583,7 +585,7 @@ inline int gemv_rows_per_wave(const Plan& p, int64_t m) {
   if (p.L > 256) return p.L % kWave == 0 && 8 * p.k >= p.W * p.row_parts ? kWave : 0;
   if (p.L != 16 && p.L != 32 && p.L != kWave) return 0;
   if (lanes <= 128 * cus) return p.C >= 96 || gemv_rows_short(p, lanes, cus) ? 16 : 0;
-  return p.L != 16 && lanes <= 256 * cus ? 32 : 0;
+  return p.L != 16 && p.C >= 64 && lanes <= 256 * cus ? 32 : 0;
 }
 
 template <class Op>

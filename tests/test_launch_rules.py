@@ -107,14 +107,15 @@ def test_one_pass_launches_of_short_lanes_hold_256_threads():
 def test_contiguous_lanes_shorter_than_a_row_tile_stay_staged():
     C = dict(order=dp.CONTIGUOUS, wg_combine=dp.TREE)
     staged = [("gemv", dict(seq_len=c, local_size=L, **C), dict(m=m, k=c * L))
-              for m, c, L in ((1024, 32, 16), (1024, 64, 32), (512, 64, 64), (64, 32, 64))]
+              for m, c, L in ((1024, 32, 16), (1024, 64, 32), (512, 64, 64), (64, 32, 64), (759, 32, 64))]
     staged += [(op, dict(seq_len=c, local_size=L, passes=p, **C), dict(n=c * L * n))
                for op in ("dot", "asum") for p in (1, 2)
                for c, L, n in ((32, 16, 256), (64, 32, 256), (64, 64, 512), (128, 64, 1000))]
     for call, l in first_kernels(staged):
         assert "rows" not in l["kernel"], (call, l)
     rows = [("gemv", dict(seq_len=c, local_size=L, **C), dict(m=m, k=k, lda=-(-k // 4) * 4))
-            for m, c, L, k in ((1024, 96, 16, 1536), (256, 64, 32, 2048), (256, 32, 16, 131))]
+            for m, c, L, k in ((1024, 96, 16, 1536), (256, 64, 32, 2048), (256, 32, 16, 131),
+                               (759, 64, 64, 4096))]
     rows += [(op, dict(seq_len=c, local_size=L, passes=2, **C), dict(n=c * L * n))
              for op in ("dot", "asum") for c, L, n in ((96, 16, 256), (128, 32, 64), (384, 64, 1000))]
     for call, l in first_kernels(rows):
